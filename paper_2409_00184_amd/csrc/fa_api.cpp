@@ -29,6 +29,7 @@ constexpr int kDefaultGrid = 768;  // 256 CUs x 3 resident workgroups (LDS bound
 // several rows restages a large lattice's slab for each; at NCP 64 one row
 // per wave runs 2.5x faster)
 constexpr int kReduceWaves = 8;
+constexpr int kSearchPairs = 256;  // (block, candidate) pairs of an NCP search's launches
 
 struct Tune {
     int rows, waves, grid, kernel, slab, store;
@@ -595,27 +596,49 @@ fa_status fa_model_errors(const fa_block *blocks, int32_t nblocks, const float *
 namespace {
 int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
+// Workspace of an NCP search that fits `group` candidates at a time and, with
+// `all`, keeps the descriptors and per-item errors of every candidate.
 struct SearchLayout {
     int64_t desc, knots, ctrl, fitws, pinv, part, total, cstride, kstride;
+    int group;
+    bool all;
 };
 
-SearchLayout search_layout(int32_t nblocks, const int32_t res[3], int32_t degree,
-                           int32_t ncp_hi) {
+SearchLayout search_layout(int32_t nblocks, const int32_t res[3], int32_t degree, int32_t ncp_hi,
+                           int group, bool all) {
     SearchLayout L{};
+    L.group = group;
+    L.all = all;
     const int64_t ncand = ncp_hi - (degree + 1) + 1;  // room for every ncp_lo
+    const int64_t kept = nblocks * (all ? ncand : 1), at_once = (int64_t)nblocks * group;
     L.cstride = align_up((int64_t)ncp_hi * ncp_hi * ncp_hi, 64);
     L.kstride = 3 * (int64_t)(ncp_hi + degree + 1);
     L.desc = 0;
-    L.knots = align_up(L.desc + (int64_t)nblocks * (int64_t)sizeof(fa_block), 256);
+    L.knots = align_up(L.desc + kept * (int64_t)sizeof(fa_block), 256);
     L.ctrl = align_up(L.knots + ncand * L.kstride * 4, 256);
-    L.fitws = align_up(L.ctrl + (int64_t)nblocks * L.cstride * 4, 256);
+    L.fitws = align_up(L.ctrl + at_once * L.cstride * 4, 256);
     // per-candidate pseudo-inverses (3 axes each)
-    L.pinv = align_up(L.fitws + fit_workspace_bytes(nblocks, res[0], res[1], ncp_hi), 256);
+    L.pinv = align_up(L.fitws + at_once * res[0] * ncp_hi * ncp_hi * 8, 256);
     L.part = align_up(L.pinv + ncand * 3 * pinv_doubles() * 8, 256);
     // (max, sum of squares) per decode item
-    L.total = align_up(L.part + (int64_t)nblocks * items_per_block(res, resolve(nullptr)) * 16,
-                       256);
+    L.total = align_up(L.part + kept * items_per_block(res, resolve(nullptr)) * 16, 256);
     return L;
+}
+
+// Candidates fitted per launch: enough that a launch works on about 256
+// (block, candidate) pairs.  Fewer leave CUs idle and make the search a chain
+// of short launches (a launch costs about 5 us whatever it does); more only
+// take memory.
+int search_group(int32_t nblocks, int32_t degree, int32_t ncp_hi) {
+    return std::max(1, std::min(kSearchPairs / nblocks, ncp_hi - degree));
+}
+
+// The bytes a search needs at least: what holds one candidate's fit of all
+// blocks (a larger workspace is used to fit several candidates at once).
+int64_t search_least(int32_t nblocks, const int32_t res[3], int32_t degree, int32_t ncp_hi) {
+    const SearchLayout L = search_layout(nblocks, res, degree, ncp_hi, 1, false);
+    return align_up(L.total + align_up(fit_workspace_bytes(nblocks, res[0], res[1], ncp_hi), 256) -
+                        (L.pinv - L.fitws), 256);
 }
 
 bool search_args_ok(int32_t nblocks, const int32_t res[3], int32_t degree, int32_t ncp_lo,
@@ -636,7 +659,9 @@ bool search_supported(const int32_t res[3], int32_t degree, int32_t ncp_hi) {
 int64_t fa_ncp_search_workspace(int32_t nblocks, const int32_t res[3], int32_t degree,
                                 int32_t ncp_hi) {
     if (nblocks <= 0 || !res_ok(res) || degree < 1 || ncp_hi < degree + 1) return -1;
-    return search_layout(nblocks, res, degree, ncp_hi).total;
+    return std::max(search_least(nblocks, res, degree, ncp_hi),
+                    search_layout(nblocks, res, degree, ncp_hi,
+                                  search_group(nblocks, degree, ncp_hi), true).total);
 }
 
 fa_status fa_ncp_search(const float *samples, int32_t nblocks, const int32_t res[3],
@@ -645,49 +670,62 @@ fa_status fa_ncp_search(const float *samples, int32_t nblocks, const int32_t res
     if (!samples || !errs || !workspace || !search_args_ok(nblocks, res, degree, ncp_lo, ncp_hi))
         return FA_ERR_INVALID_ARG;
     if (!search_supported(res, degree, ncp_hi)) return FA_ERR_UNSUPPORTED;
-    const SearchLayout L = search_layout(nblocks, res, degree, ncp_hi);
-    if (workspace_bytes < L.total || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
+    if (workspace_bytes < search_least(nblocks, res, degree, ncp_hi) ||
+        (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
         return FA_ERR_INVALID_ARG;
+    SearchLayout L = search_layout(nblocks, res, degree, ncp_hi,
+                                   search_group(nblocks, degree, ncp_hi), true);
+    if (workspace_bytes < L.total) L = search_layout(nblocks, res, degree, ncp_hi, 1, false);
     hipStream_t s = (hipStream_t)stream;
     char *w = static_cast<char *>(workspace);
     fa_block *desc = reinterpret_cast<fa_block *>(w + L.desc);
     float *knots = reinterpret_cast<float *>(w + L.knots);
     float *ctrl = reinterpret_cast<float *>(w + L.ctrl);
+    double *part = reinterpret_cast<double *>(w + L.part);
+    double *xall = reinterpret_cast<double *>(w + L.pinv);
     const int ncand = ncp_hi - ncp_lo + 1;
+    const int64_t stride = 2 * (int64_t)ncand;
     Tune t = resolve(nullptr);
     t.waves = kReduceWaves;
     const int64_t vox = (int64_t)res[0] * res[1] * res[2];
-    double *xall = reinterpret_cast<double *>(w + L.pinv);
+    const int per = (int)items_per_block(res, t);
     // every candidate's knots and pseudo-inverses depend on (n, p, res) only:
     // built once for all candidates, in one launch
     hipError_t e = launch_pinv_candidates(knots, ncp_lo, ncand, degree, (int)L.kstride, res[0],
                                           res[1], res[2], xall, s);
-    if (e != hipSuccess) return FA_ERR_DEVICE;
+    if (e == hipSuccess && L.all)
+        e = launch_candidates(desc, nblocks, ncand, ncp_hi, ncp_lo, degree, L.group,
+                              (int)L.kstride, L.cstride, s);
     // from the largest NCP down, as the in-level search runs (Sec. 4.2.1)
-    for (int n = ncp_hi; n >= ncp_lo; --n) {
-        float *kn = knots + (int64_t)(n - ncp_lo) * L.kstride;
-        e = launch_candidate(desc, kn, nblocks, n, degree, L.cstride, s);
-        if (e != hipSuccess) return FA_ERR_DEVICE;
-        e = launch_fit_shared(desc, nblocks, kn, res[0], res[1], res[2], n, samples,
-                              reinterpret_cast<double *>(w + L.fitws), xall + (int64_t)(n - ncp_lo) * 3 * pinv_doubles(),
-                              ctrl, s);
-        if (e != hipSuccess) return FA_ERR_DEVICE;
-        // the candidate's value decode reduced straight to its error-map
-        // entry (the decode itself is never stored)
-        DecodeLaunch a = grid_args(desc, nblocks, kn, ctrl, FA_F32, res, 1u, t, nullptr,
+    for (int c = 0; c < ncand && e == hipSuccess; c += L.group) {
+        const int n = ncp_hi - c, cnt = std::min(L.group, ncand - c);
+        if (!L.all)
+            e = launch_candidates(desc, nblocks, 1, n, ncp_lo, degree, 1, (int)L.kstride,
+                                  L.cstride, s);
+        fa_block *dc = desc + (L.all ? (int64_t)c * nblocks : 0);
+        if (e == hipSuccess)
+            e = launch_fit_candidates(dc, nblocks, cnt, res[0], res[1], res[2], n, samples,
+                                      xall + (int64_t)(n - ncp_lo) * 3 * pinv_doubles(),
+                                      reinterpret_cast<double *>(w + L.fitws), ctrl, s);
+        if (e != hipSuccess) break;
+        // the candidates' value decodes reduced straight to their error-map
+        // entries (the decodes themselves are never stored)
+        DecodeLaunch a = grid_args(dc, nblocks * cnt, knots, ctrl, FA_F32, res, 1u, t, nullptr,
                                    nullptr, nullptr);
         a.samples = samples;
-        a.partials = reinterpret_cast<double *>(w + L.part);
-        a.errs = errs + 2 * (n - ncp_lo);
-        a.errs_stride = 2 * (int64_t)ncand;
-        e = launch_decode_sep(a, t.waves, (int)std::min<int64_t>(a.nitems, default_grid(t, a.nitems)),
-                              s);
-        if (e == hipSuccess)
-            e = launch_errors_combine(a.partials, nblocks, a.nrowt * a.ncolt, vox, a.errs,
-                                      a.errs_stride, s);
-        if (e != hipSuccess) return FA_ERR_DEVICE;
+        a.nsrc = nblocks;
+        a.partials = part + (L.all ? (int64_t)c * nblocks * per * 2 : 0);
+        a.error_form = 1;
+        e = launch_decode_sep(a, t.waves,
+                              (int)std::min<int64_t>(a.nitems, default_grid(t, a.nitems)), s);
+        if (e == hipSuccess && !L.all)
+            e = launch_errors_combine(part, nblocks, 1, per, vox, errs + 2 * (n - ncp_lo), stride,
+                                      s);
     }
-    return FA_OK;
+    if (e == hipSuccess && L.all)
+        e = launch_errors_combine(part, nblocks, ncand, per, vox, errs + 2 * (ncand - 1), stride,
+                                  s);
+    return e == hipSuccess ? FA_OK : FA_ERR_DEVICE;
 }
 
 fa_status fa_ncp_select(const float *errs, int32_t nblocks, int32_t ncand, int32_t ncp_lo,

@@ -189,7 +189,7 @@ __device__ void sep_item(const DecodeLaunch &a, int b, int row0, int nrows, int 
     double acc = 0.0;
     float amax = 0.0f;
     const __amdgpu_buffer_rsrc_t yr =
-        make_rsrc(RESID ? a.samples + (int64_t)b * vox : a.out, RESID ? (uint32_t)vox * 4u : 0u);
+        make_rsrc(RESID ? a.samples + (int64_t)(MODE == 2 ? b % a.nsrc : b) * vox : a.out, RESID ? (uint32_t)vox * 4u : 0u);
     const __amdgpu_buffer_rsrc_t gr =
         make_rsrc(GRAD ? a.out + (int64_t)b * vox : a.samples, GRAD ? (uint32_t)vox * 4u : 0u);
 
@@ -509,19 +509,20 @@ __global__ void residual_combine_kernel(const double *partials, int nblocks, int
     sumsq[b] = t;
 }
 
-// errs[b * stride + {0, 1}] = (max, sqrt(sum / vox)) of block b's per-item
-// (max, sum of squares) partials, in item order
-__global__ void errors_combine_kernel(const double *partials, int nblocks, int per, int64_t vox,
-                                      float *errs, int64_t stride) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nblocks) return;
+// errs[b * stride - 2 c + {0, 1}] = (max, sqrt(sum / vox)) of block b under
+// candidate c from its per-item (max, sum of squares) partials, in item order
+__global__ void errors_combine_kernel(const double *partials, int nblocks, int ncand, int per,
+                                      int64_t vox, float *errs, int64_t stride) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= nblocks * ncand) return;
     double m = 0.0, t = 0.0;
     for (int k = 0; k < per; ++k) {
-        m = fmax(m, partials[2 * ((int64_t)b * per + k)]);
-        t += partials[2 * ((int64_t)b * per + k) + 1];
+        m = fmax(m, partials[2 * ((int64_t)e * per + k)]);
+        t += partials[2 * ((int64_t)e * per + k) + 1];
     }
-    errs[(int64_t)b * stride] = (float)m;
-    errs[(int64_t)b * stride + 1] = (float)sqrt(t / (double)vox);
+    float *o = errs + (int64_t)(e % nblocks) * stride - 2 * (e / nblocks);
+    o[0] = (float)m;
+    o[1] = (float)sqrt(t / (double)vox);
 }
 
 }  // namespace
@@ -554,7 +555,7 @@ hipError_t launch_sep(const DecodeLaunch &a, int waves, int grid, hipStream_t s)
 }
 
 hipError_t launch_decode_sep(const DecodeLaunch &a, int waves, int grid, hipStream_t s) {
-    if (a.samples && a.errs) return launch_sep<false, 2>(a, waves, grid, s);
+    if (a.samples && a.error_form) return launch_sep<false, 2>(a, waves, grid, s);
     if (a.interleave)
         return a.nt_store ? launch_sep<true, 3>(a, waves, grid, s)
                           : launch_sep<false, 3>(a, waves, grid, s);
@@ -572,10 +573,10 @@ hipError_t launch_residual_combine(const double *partials, int nblocks, int per,
     return hipGetLastError();
 }
 
-hipError_t launch_errors_combine(const double *partials, int nblocks, int per, int64_t vox,
-                                 float *errs, int64_t stride, hipStream_t s) {
-    hipLaunchKernelGGL(errors_combine_kernel, dim3((nblocks + 255) / 256), dim3(256), 0, s,
-                       partials, nblocks, per, vox, errs, stride);
+hipError_t launch_errors_combine(const double *partials, int nblocks, int ncand, int per,
+                                 int64_t vox, float *errs, int64_t stride, hipStream_t s) {
+    hipLaunchKernelGGL(errors_combine_kernel, dim3((nblocks * ncand + 255) / 256), dim3(256), 0, s,
+                       partials, nblocks, ncand, per, vox, errs, stride);
     return hipGetLastError();
 }
 

@@ -6,7 +6,7 @@
 // collocation matrices B_a[i][j] = N_j(u_i) on the decode grid, so the
 // least-squares lattice is P = y x_1 X_x x_2 X_y x_3 X_z with the
 // pseudo-inverses X_a = B_a^+ = (B_a^T B_a)^{-1} B_a^T (n_a x R_a).  Each X_a
-// is built in FP64 inside the workgroup that needs it: the basis at the
+// is built in FP64: the basis at the
 // grid points in FP64 (same spans as the decode), the band Gram matrix
 // B_a^T B_a (half-bandwidth p), its band Cholesky factor, and one
 // forward/backward solve per grid point.  Forming X_a first and applying it
@@ -14,14 +14,13 @@
 // number of B_a, where solving the normal equations on B^T y would square
 // it (the collocation matrix of NCP close to R on the uniform grid is
 // badly conditioned).  Three kernels, FP64 throughout:
-//   fit_pinv: X_a of every (block, axis), one workgroup each, into the
-//           caller's workspace,
-//   fit_z:  T[b][k][x][y] = sum_z X_z[k][z] y[b][x][y][z]   (chunks of 128
-//           (x, y) lines staged in LDS, T in the workspace),
-//   fit_xy: for each k, P[:, :, k] = X_x T[b][k] X_y^T        (one workgroup
-//           per (block, group of k), the slice in LDS, X_x T in registers),
-// the dense products of fit_z and fit_xy on the FP64 matrix cores
-// (v_mfma_f64_16x16x4f64), and the lattice rounded to FP32 once.
+//   fit_pinv: X_a of every (block, axis), one wave each, into the caller's
+//           workspace,
+//   fit_zy: U[b][x] = X_y y[b][x] X_z^T for every x slice (one wave per slice,
+//           both products in registers, U in the workspace),
+//   fit_x:  P[b] = X_x U[b], a product over the lattice's contiguous (j, k),
+// the dense products on the FP64 matrix cores (v_mfma_f64_16x16x4f64), and
+// the lattice rounded to FP32 once.
 // residual kernel: one workgroup per block reduces y - f to (max |r|,
 // sqrt(mean r^2)) in a fixed order (deterministic).
 #include <algorithm>
@@ -58,77 +57,96 @@ __device__ __forceinline__ void basis64(const float *t, int s, double u, int p, 
     }
 }
 
-struct PinvScratch {
+// One wave per pseudo-inverse, lane i solving for grid point i, so the
+// build needs no barrier and four of them share a CU.  What bounds it is the
+// serial chain of the band factorisation and of the two substitutions along
+// j: the factor keeps reciprocal diagonals (one product a step where a
+// division stood), and the last p values of a recursion stay in registers.
+struct PinvSmem {
     double N[kFitR][4];
-    int span[kFitR];
-    double G[kFitN][4];  // G[j][d] = G(j, j + d)
-    double L[kFitN][4];  // L[j][d] = L(j, j - d)
+    int first[kFitN + 8];    // first grid point on span s or a later one
+    double G[kFitN + 1][4];  // G[j][d] = G(j, j + d)
+    double L[kFitN + 3][4];  // L[j][d] = L(j, j - d), L[j][0] = 1 / L(j, j); zero rows after n
+    double Z[kFitN][kFitR];  // forward substitution, column i
 };
 
-// X = B^+ of one axis (n functions of degree p, knots t, R grid points),
-// written as X[j * sj + i * si] for j < n, i < R.  All threads of the
-// workgroup take part; ends with a barrier.
-__device__ void build_pinv(PinvScratch &w, const float *t, int n, int p, int R, double *X,
-                           int sj, int si) {
-    const int tid = threadIdx.x;
-    for (int i = tid; i < R; i += kFitThreads) {
+// X = B^+ of one axis (n functions of degree p, knots t, R grid points) as
+// X[j * kFitR + i], j < n; columns i >= R are zero.
+__device__ void build_pinv(PinvSmem &w, const float *t, int n, int p, int R, double *X) {
+    const int i = threadIdx.x;  // one wave
+    double Nv[4] = {0.0, 0.0, 0.0, 0.0};
+    int s = 0;
+    if (i < R) {
         const float uf = grid_pos(i, R);
-        const int s = span_search(n, p, t, uf);
-        double Nv[4];
+        s = span_search(n, p, t, uf);
         basis64(t, s, (double)uf, p, Nv);
-        w.span[i] = s;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) w.N[i][r] = Nv[r];
     }
+    // first[t] = i for the spans t after the previous point's up to this one's
+    const int before = __shfl_up(s, 1);
+    if (i < R)
+        for (int t = i == 0 ? 0 : before + 1; t <= s; ++t) w.first[t] = i;
+    if (i == R - 1)
+        for (int t = s + 1; t <= n + p; ++t) w.first[t] = R;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w.N[i][r] = Nv[r];
+    if (i < 3)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) w.L[n + i][d] = 0.0;
     __syncthreads();
-    for (int e = tid; e < n * 4; e += kFitThreads) {
+    for (int e = i; e < n * 4; e += kWave) {
         const int j = e >> 2, d = e & 3;
         double g = 0.0;
+        // points on spans j + d .. j + p, in order: on span t, function j is
+        // N[j - t + p]
         if (d <= p)
-            for (int i = 0; i < R; ++i) {
-                const int r = j - (w.span[i] - p);
-                if (r >= 0 && r + d <= p) g += w.N[i][r] * w.N[i][r + d];
-            }
+            for (int t = j + d; t <= j + p; ++t)
+                for (int q = w.first[t]; q < w.first[t + 1]; ++q)
+                    g += w.N[q][j - t + p] * w.N[q][j - t + p + d];
         w.G[j][d] = g;
     }
     __syncthreads();
-    if (tid == 0) {  // band Cholesky G = L L^T
+    {  // band Cholesky G = L L^T: row j from rows j - 1 .. j - 3, every lane the same
+        double a1[4] = {0, 0, 0, 0}, a2[4] = {0, 0, 0, 0}, a3[4] = {0, 0, 0, 0};  // L rows j-1, j-2, j-3
         for (int j = 0; j < n; ++j) {
-            for (int d = p; d >= 1; --d) {
-                const int k = j - d;
-                if (k < 0) {
-                    w.L[j][d] = 0.0;
-                    continue;
-                }
-                double v = w.G[k][d];
-                for (int m = d + 1; m <= p; ++m)
-                    if (j - m >= 0) v -= w.L[j][m] * w.L[k][m - d];
-                w.L[j][d] = v / w.L[k][0];
+            double c[4] = {0.0, 0.0, 0.0, 0.0};
+            if (p >= 3 && j >= 3) c[3] = w.G[j - 3][3] * a3[0];
+            if (p >= 2 && j >= 2) c[2] = (w.G[j - 2][2] - c[3] * a2[1]) * a2[0];
+            if (j >= 1) c[1] = (w.G[j - 1][1] - c[3] * a1[2] - c[2] * a1[1]) * a1[0];
+            c[0] = rsqrt(w.G[j][0] - c[3] * c[3] - c[2] * c[2] - c[1] * c[1]);
+            if (i < 4) w.L[j][i] = i == 0 ? c[0] : (i == 1 ? c[1] : (i == 2 ? c[2] : c[3]));
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                a3[d] = a2[d];
+                a2[d] = a1[d];
+                a1[d] = c[d];
             }
-            double v = w.G[j][0];
-            for (int d = 1; d <= p; ++d) v -= w.L[j][d] * w.L[j][d];
-            w.L[j][0] = sqrt(v);
         }
     }
     __syncthreads();
     // column i of X solves G x = B[i, :]^T (non-zero at s_i - p .. s_i)
-    for (int i = tid; i < R; i += kFitThreads) {
-        const int j0 = w.span[i] - p;
-        for (int j = 0; j < n; ++j) {  // forward: L z = rhs
-            double v = (j >= j0 && j <= j0 + p) ? w.N[i][j - j0] : 0.0;
-            if (j > j0)
-                for (int d = 1; d <= p; ++d)
-                    if (j - d >= j0) v -= w.L[j][d] * X[(j - d) * sj + i * si];
-            X[j * sj + i * si] = j >= j0 ? v / w.L[j][0] : 0.0;
-        }
-        for (int j = n - 1; j >= 0; --j) {  // backward: L^T x = z
-            double v = X[j * sj + i * si];
-            for (int d = 1; d <= p; ++d)
-                if (j + d < n) v -= w.L[j + d][d] * X[(j + d) * sj + i * si];
-            X[j * sj + i * si] = v / w.L[j][0];
-        }
+    const int j0 = s - p;
+    double z1 = 0.0, z2 = 0.0, z3 = 0.0;
+#pragma unroll 4
+    for (int j = 0; j < n; ++j) {  // forward: L z = rhs
+        const int r = j - j0;
+        double v = r == 0 ? Nv[0] : (r == 1 ? Nv[1] : (r == 2 ? Nv[2] : (r == 3 ? Nv[3] : 0.0)));
+        v = v - w.L[j][3] * z3 - w.L[j][2] * z2 - w.L[j][1] * z1;
+        v = (i < R && r >= 0) ? v * w.L[j][0] : 0.0;
+        w.Z[j][i] = v;
+        z3 = z2;
+        z2 = z1;
+        z1 = v;
     }
-    __syncthreads();
+    double x1 = 0.0, x2 = 0.0, x3 = 0.0;
+#pragma unroll 4
+    for (int j = n - 1; j >= 0; --j) {  // backward: L^T x = z
+        double v = w.Z[j][i] - w.L[j + 3][3] * x3 - w.L[j + 2][2] * x2 - w.L[j + 1][1] * x1;
+        v = i < R ? v * w.L[j][0] : 0.0;
+        X[j * kFitR + i] = v;
+        x3 = x2;
+        x2 = x1;
+        x1 = v;
+    }
 }
 
 __device__ __forceinline__ const float *axis_knots(const float *knots, const fa_block &b, int a) {
@@ -140,27 +158,20 @@ __device__ __forceinline__ const float *axis_knots(const float *knots, const fa_
 
 constexpr int64_t kPinvStride = (int64_t)kFitN * kFitR;  // doubles per (block, axis)
 
-struct PinvSmem {
-    double X[kFitN][kFitR];
-    PinvScratch w;
-};
+__device__ __forceinline__ int uni32(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Xg[(b * 3 + a) * kPinvStride + j * kFitR + i] = X_a[j][i]
-__global__ __launch_bounds__(kFitThreads) void fit_pinv_kernel(const fa_block *blocks,
-                                                               int nblocks, const float *knots,
-                                                               int r0, int r1, int r2,
-                                                               double *Xg) {
+__global__ __launch_bounds__(kWave) void fit_pinv_kernel(const fa_block *blocks, int nblocks,
+                                                         const float *knots, int r0, int r1,
+                                                         int r2, double *Xg) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     PinvSmem &sm = *reinterpret_cast<PinvSmem *>(smem_raw);
     for (int64_t item = blockIdx.x; item < (int64_t)nblocks * 3; item += gridDim.x) {
         const int bi = (int)(item / 3), a = (int)(item - (int64_t)bi * 3);
         const fa_block b = blocks[bi];
         const int n = a == 0 ? b.ncp[0] : (a == 1 ? b.ncp[1] : b.ncp[2]);
-        const int p = a == 0 ? b.degree[0] : (a == 1 ? b.degree[1] : b.degree[2]);
         const int Ra = a == 0 ? r0 : (a == 1 ? r1 : r2);
-        build_pinv(sm.w, axis_knots(knots, b, a), n, p, Ra, &sm.X[0][0], kFitR, 1);
-        double *dst = Xg + item * kPinvStride;
-        for (int e = threadIdx.x; e < n * kFitR; e += kFitThreads) dst[e] = (&sm.X[0][0])[e];
+        build_pinv(sm, axis_knots(knots, b, a), n, b.degree[0], Ra, Xg + item * kPinvStride);
         __syncthreads();
     }
 }
@@ -178,21 +189,18 @@ __device__ __forceinline__ float candidate_knot(int j, int n, int p) {
 // candidates in one launch: knots of candidate c (n = ncp_lo + c) at
 // kall + c * kstride (x, y, z vectors back to back), X_a at
 // xall + (c * 3 + a) * kPinvStride.
-__global__ __launch_bounds__(kFitThreads) void pinv_candidates_kernel(float *kall, int ncp_lo,
-                                                                      int ncand, int p,
-                                                                      int kstride, int r0, int r1,
-                                                                      int r2, double *xall) {
+__global__ __launch_bounds__(kWave) void pinv_candidates_kernel(float *kall, int ncp_lo, int ncand,
+                                                                int p, int kstride, int r0, int r1,
+                                                                int r2, double *xall) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     PinvSmem &sm = *reinterpret_cast<PinvSmem *>(smem_raw);
     for (int item = blockIdx.x; item < ncand * 3; item += gridDim.x) {
         const int c = item / 3, a = item - 3 * c, n = ncp_lo + c, nk = n + p + 1;
         float *t = kall + (int64_t)c * kstride + a * nk;
-        for (int j = threadIdx.x; j < nk; j += kFitThreads) t[j] = candidate_knot(j, n, p);
+        for (int j = threadIdx.x; j < nk; j += kWave) t[j] = candidate_knot(j, n, p);
         __syncthreads();
         const int Ra = a == 0 ? r0 : (a == 1 ? r1 : r2);
-        build_pinv(sm.w, t, n, p, Ra, &sm.X[0][0], kFitR, 1);
-        double *dst = xall + (int64_t)item * kPinvStride;
-        for (int e = threadIdx.x; e < n * kFitR; e += kFitThreads) dst[e] = (&sm.X[0][0])[e];
+        build_pinv(sm, t, n, p, Ra, xall + (int64_t)item * kPinvStride);
         __syncthreads();
     }
 }
@@ -201,244 +209,274 @@ __global__ __launch_bounds__(kFitThreads) void pinv_candidates_kernel(float *kal
 // A[l%16][l/16] and B[l/16][l%16] from lane l and returns D[4r + l/16][l%16]
 // in component r (layout checked on the device).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-constexpr int kXS = kFitR + 1;  // padded row of an LDS matrix (doubles)
-
-constexpr int kZLines = 128;  // (x, y) lines per fit_z chunk: two workgroups per CU
-
-struct FitZSmem {
-    double X[kFitN][kXS];                 // X_z[k][z]
-    float ys[kZLines][kFitR + 1];         // staged lines (padded)
+// Arguments of the two products of a fit.  Entry e of `blocks` is fitted to
+// the samples of block e % nsrc; its pseudo-inverses start at X + (e / nsrc)
+// * xcand + (e % nsrc) * xstride, its intermediate at T + e * tstride.
+struct FitArgs {
+    const fa_block *blocks;
+    int nblocks, nsrc;
+    int r0, r1, r2, max_n;
+    const float *y;
+    const double *X;
+    int64_t xcand, xstride;
+    double *T;
+    int64_t tstride;
+    float *ctrl;
 };
 
-// T[b][k][l] = sum_z X_z[k][z] y[b][l][z], l = x * R1 + y: per chunk of 128
-// lines, a (n_z x R2) x (R2 x 128) product on the FP64 matrix cores.  A
-// workgroup takes `cgroup` consecutive chunks of one block: X_z is staged
-// once, and the next chunk's samples are loaded into registers while the
-// products of the current one run.
-constexpr int kZRegs = kZLines * kFitR / kFitThreads;  // chunk floats per thread
+__device__ __forceinline__ const double *fit_x_of(const FitArgs &a, int bi) {
+    return a.X + (bi / a.nsrc) * a.xcand + (bi % a.nsrc) * a.xstride;
+}
 
-__global__ __launch_bounds__(kFitThreads) void fit_z_kernel(const fa_block *blocks, int nblocks,
-                                                            const float *knots, int r0, int r1,
-                                                            int r2, int max_n, int cgroup,
-                                                            const float *y, const double *Xg,
-                                                            int64_t xstride, double *T) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    FitZSmem &sm = *reinterpret_cast<FitZSmem *>(smem_raw);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int lr = lane & 15, lk = lane >> 4;
-    const int64_t lines = (int64_t)r0 * r1;
-    const int chunks = (int)((lines + kZLines - 1) / kZLines);
-    const int groups = (chunks + cgroup - 1) / cgroup;
-    for (int64_t item = blockIdx.x; item < (int64_t)nblocks * groups; item += gridDim.x) {
-        const int bi = (int)(item / groups);
-        const int c0 = (int)(item - (int64_t)bi * groups) * cgroup;
-        const int c1 = min(chunks, c0 + cgroup);
-        const fa_block b = blocks[bi];
-        const int nz = b.ncp[2];
-        if (nz > max_n) continue;  // the workspace has no room; the lattice is left as is
-        __syncthreads();  // the previous item is done with the LDS
-        const double *Xz = Xg + (int64_t)bi * xstride + 2 * kPinvStride;
-        for (int e = tid; e < nz * kFitR; e += kFitThreads) {
-            const int k = e / kFitR;
-            sm.X[k][e - k * kFitR] = Xz[e];
-        }
-        // chunk c in registers: element e = tid + kFitThreads m of its cl x r2 samples
-        float yv[kZRegs];
-        auto fetch = [&](int c) {
-            const int64_t l0 = (int64_t)c * kZLines;
-            const int cl = (int)(lines - l0 < kZLines ? lines - l0 : kZLines);
-            const float *yb = y + ((int64_t)bi * lines + l0) * r2;
+constexpr uint32_t kDeadFit = 0x40000000u;      // offset beyond every buffer (also twice)
+constexpr int kZyWaves = 4;                     // waves per fit_zy workgroup
+constexpr int kOpSteps = kFitR / 4;             // K steps of a 64-long contraction
+constexpr int kOpTile = kOpSteps * kWave;       // doubles of one 16-row operand table
+
+// U[x][j][k] = sum_y X_y[j][y] sum_z X_z[k][z] y[x][y][z] of one x slice,
+// both products on the FP64 matrix cores without leaving the wave's
+// registers: the z product of a 16-row band of the slice leaves Z[yy][k] in
+// exactly the B operand of four K steps of the y product (component r of
+// band t: row 16t + 4r + l/16, column l%16).  A lane reads four consecutive
+// samples of its rows with one 16-byte load (the K order of the z product
+// is permuted to z = 16q + 4(l/16) + j), so a slice goes from memory to U
+// without LDS or a barrier; the operands of X_z and X_y sit in LDS in lane
+// order.
+//
+// Bound by the FP64 matrix cores (64 cycles per product, n_z / 16 tiles of
+// 16 NT + 16 NJ products a slice), busy 61% of the time: 260 us for 512
+// blocks of 64^3 at NCP 32, where a pair of kernels that kept T[k][x][y]
+// between the products (64 / n times larger than U) and staged the operands
+// of both through LDS between barriers took 850 us with the x product in it
+// (now 108 us, fit_x below).
+template <int NT, int NJ>
+__device__ __forceinline__ void fit_zy_slice(const double *oz, const double *oy, u32x4 (&s)[4][4],
+                                             int nq, int nk, int ny, int nz, int lane,
+                                             __amdgpu_buffer_rsrc_t U, uint32_t u0) {
+    for (int kt = 0; kt < nk; ++kt) {
+        // opaque to the compiler, so that it keeps neither the y operands nor
+        // (below) the converted samples in registers from k tile to k tile
+        asm volatile("" : "+v"(lane));
+        const double *bz = oz + kt * kOpTile + lane;
+        f64x4 Z[NT];
 #pragma unroll
-            for (int m = 0; m < kZRegs; ++m) {
-                const int e = tid + kFitThreads * m;
-                yv[m] = (c < c1 && e < cl * r2) ? yb[e] : 0.0f;
-            }
-        };
-        fetch(c0);
-        const int mt = (nz + 15) >> 4, ksteps = (r2 + 3) >> 2;
-        for (int c = c0; c < c1; ++c) {
-            const int64_t l0 = (int64_t)c * kZLines;
-            const int cl = (int)(lines - l0 < kZLines ? lines - l0 : kZLines);
-            if (c > c0) __syncthreads();  // the previous chunk's products are done
+        for (int t = 0; t < NT; ++t) Z[t] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int m = 0; m < kZRegs; ++m) {
-                const int e = tid + kFitThreads * m;
-                if (e < cl * r2) {
-                    const int li = e / r2;
-                    sm.ys[li][e - li * r2] = yv[m];
-                }
-            }
-            __syncthreads();
-            fetch(c + 1);  // in flight during this chunk's products
-            const int nt = (cl + 15) >> 4;
-            const int nst = (nt + 3) >> 2;  // strips of 4 line tiles sharing the A operand
-            double *Tb = T + (int64_t)bi * max_n * lines + l0;
-            for (int unit = wave; unit < mt * nst; unit += kFitThreads / 64) {
-                const int ti = unit / nst, tj0 = 4 * (unit - ti * nst);
-                const int k = 16 * ti + lr;
-                f64x4 acc[4];
+        for (int q = 0; q < 4; ++q) {
+            if (q >= nq) break;  // uniform: no samples there
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
-                for (int ks = 0; ks < ksteps; ++ks) {
-                    const int z = 4 * ks + lk;
-                    const bool zok = z < r2;
-                    const double av = (k < nz && zok) ? sm.X[k][z] : 0.0;
+            for (int j = 0; j < 4; ++j) {
+                const double b = bz[(4 * q + j) * kWave];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int li = 16 * (tj0 + q) + lr;
-                        const double bv = (li < cl && zok) ? (double)sm.ys[li][z] : 0.0;
-                        acc[q] = mfma64(av, bv, acc[q]);  // four independent chains
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int kk = 16 * ti + 4 * r + lk, ll = 16 * (tj0 + q) + lr;
-                        if (kk < nz && ll < cl) Tb[(int64_t)kk * lines + ll] = acc[q][r];
-                    }
+                for (int t = 0; t < NT; ++t)  // independent chains
+                    Z[t] = mfma64((double)__uint_as_float(s[t][q][j]), b, Z[t]);
             }
         }
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(s[t][q]));
+        f64x4 Y[NJ];
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) Y[jt] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int jt = 0; jt < NJ; ++jt)
+                    Y[jt] = mfma64(oy[jt * kOpTile + (4 * t + r) * kWave + lane], Z[t][r], Y[jt]);
+        const int j = lane >> 4, k = 16 * kt + (lane & 15);
+        const uint32_t at = k < nz ? (uint32_t)(j * nz + k) * 8u : kDeadFit;
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                __builtin_amdgcn_raw_buffer_store_b64(
+                    __builtin_bit_cast(u32x2, (double)Y[jt][r]), U,
+                    16 * jt + 4 * r + j < ny ? at : kDeadFit,
+                    u0 + (uint32_t)((16 * jt + 4 * r) * nz) * 8u, 0);
+            }
     }
 }
 
-struct FitXYSmem {
-    double Xy[kFitN][kXS];  // X_y[j][y]
-    double S[kFitR][kXS];   // slice T[b][k] as [x][y]
-};
-
-// For each k: P[:, :, k] = X_x T[b][k] X_y^T, two products on the FP64
-// matrix cores, one workgroup per (b, group of k), wave w owning rows
-// 16w..16w+15 of P.  The first product is formed transposed, U^T = S^T X_x^T:
-// its accumulator layout (row 4r + l/16, column l%16 in component r of lane
-// l) is then exactly the A operand of the second product U X_y^T for the K
-// steps 4t + r (t = the U^T tile), so U never leaves registers; the wave's
-// X_x rows are held in registers as the B operand of the first product for
-// every k of the group.  LDS holds X_y and the slice only (two workgroups
-// per CU); the next k's slice is loaded into registers while the products
-// of this one run, and the second product runs over the block's j tiles
-// only (one straight-line instance per tile count).
-constexpr int kSliceRegs = kFitR * kFitR / kFitThreads;  // slice doubles per thread
-
-template <int NQ>
-__device__ __forceinline__ void fit_xy_slice(const FitXYSmem &sm, int wave, int lr, int lk,
-                                             int r0, int r1, int nx, int ny, int nz, int k,
-                                             const double (&xb)[kFitR / 4], float *Pb) {
-    constexpr int kKS = kFitR / 4;  // K steps of a 64-long contraction
-    // U^T[yy][i] for the yy tiles t: A = S^T[yy][x] = S[x][yy]
-    f64x4 u[4];
+template <int NT, int NJ>
+__device__ __forceinline__ void fit_zy_block(const FitArgs &a, int bi, int x0, int x1, int ny, int nz,
+                                             const double *oz, const double *oy) {
+    const int wave = uni32(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int gq = lane >> 4, l16 = lane & 15;
+    const int r1 = a.r1, r2 = a.r2;
+    const uint32_t slice = (uint32_t)r1 * (uint32_t)r2 * 4u;
+    // rows and columns outside the slice load at an offset beyond the
+    // resource and read as zero
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(
+        a.y + (int64_t)(bi % a.nsrc) * a.r0 * r1 * r2, (uint32_t)a.r0 * slice);
+    uint32_t row[4], col[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) u[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-    // every K step and tile runs (entries outside the slice are selected to
-    // zero: no scalar conditions in the unrolled chains)
-#pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) {
-        const int x = 4 * ks + lk;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int yy = 16 * t + lr;
-            const double sv = sm.S[x][yy];
-            u[t] = mfma64((yy < r1 && x < r0) ? sv : 0.0, xb[ks], u[t]);
-        }
+    for (int t = 0; t < 4; ++t) {
+        row[t] = 16 * t + l16 < r1 ? (uint32_t)((16 * t + l16) * r2) * 4u : kDeadFit;
+        col[t] = 16 * t + 4 * gq < r2 ? (uint32_t)(16 * t + 4 * gq) * 4u : kDeadFit;
     }
-    // P[i][j] = sum_yy U[i][yy] X_y[j][yy]: A for K step 4t + r is component
-    // r of u[t] (U[16 wave + l%16][4(4t + r) + l/16]), over the NQ j tiles
-    f64x4 acc[NQ];
+    const bool ragged = (r2 & 3) != 0;
+    auto load = [&](uint32_t at, u32x4(&s)[4][4]) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int yy = 4 * (4 * t + r) + lk;
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int j = 16 * q + lr;
-                const double xv = sm.Xy[j][yy];
-                acc[q] = mfma64(u[t][r], (j < ny && yy < r1) ? xv : 0.0, acc[q]);
+            for (int q = 0; q < 4; ++q) {
+                s[t][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, row[t] + col[q], at, 0);
             }
-        }
+    };
+    auto trim = [&](u32x4(&s)[4][4]) {  // the part of the last load past its row's end
+        if (!ragged) return;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int ii = 16 * wave + 4 * r + lk, jj = 16 * q + lr;
-            if (ii < nx && jj < ny) Pb[((int64_t)ii * ny + jj) * nz + k] = (float)acc[q][r];
-        }
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (16 * q + 4 * gq + j >= r2) s[t][q][j] = 0u;
+    };
+    const int nq = (r2 + 15) >> 4, nk = (nz + 15) >> 4;
+    const uint32_t ub = (uint32_t)(ny * nz) * 8u;  // bytes of U of a slice
+    const __amdgpu_buffer_rsrc_t U = make_rsrc(a.T + (int64_t)bi * a.tstride, (uint32_t)a.r0 * ub);
+    u32x4 cur[4][4], nxt[4][4];
+    int x = x0 + wave;
+    if (x < x1) load((uint32_t)x * slice, cur);
+    for (; x < x1; x += kZyWaves) {
+        // the next slice, in flight during all of this one
+        load(x + kZyWaves < x1 ? (uint32_t)(x + kZyWaves) * slice : kDeadFit, nxt);
+        trim(cur);
+        fit_zy_slice<NT, NJ>(oz, oy, cur, nq, nk, ny, nz, lane, U, (uint32_t)x * ub);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cur[t][q] = nxt[t][q];
+    }
 }
 
-__global__ __launch_bounds__(kFitThreads) void fit_xy_kernel(const fa_block *blocks, int nblocks,
-                                                             const float *knots, int r0, int r1,
-                                                             int max_n, int kgroup,
-                                                             const double *Xg, int64_t xstride,
-                                                             const double *T, float *ctrl) {
+// One workgroup per (block, group of x slices); wave w takes slices w, w + 4, ...
+template <int NT>
+__global__ __launch_bounds__(kZyWaves * 64, 2) void fit_zy_kernel(FitArgs a, int xgroup) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    FitXYSmem &sm = *reinterpret_cast<FitXYSmem *>(smem_raw);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int lr = lane & 15, lk = lane >> 4;
-    constexpr int kKS = kFitR / 4;  // K steps of a 64-long contraction
-    const int lines = r0 * r1;
-    const int groups = (max_n + kgroup - 1) / kgroup;
-    for (int64_t item = blockIdx.x; item < (int64_t)nblocks * groups; item += gridDim.x) {
-        const int bi = (int)(item / groups);
-        const int k0 = (int)(item - (int64_t)bi * groups) * kgroup;
-        const fa_block b = blocks[bi];
-        const int nx = b.ncp[0], ny = b.ncp[1], nz = b.ncp[2];
-        if (k0 >= nz || nz > max_n) continue;
-        const double *Xx = Xg + (int64_t)bi * xstride;
-        const double *Xy = Xx + kPinvStride;
-        for (int e = tid; e < ny * kFitR; e += kFitThreads) {
-            const int j = e / kFitR;
-            sm.Xy[j][e - j * kFitR] = Xy[e];
-        }
-        // B operand of U^T = S^T X_x^T: X_x[i][x], i = 16 wave + l%16, x = 4 ks + l/16
-        const int i = 16 * wave + lr;
-        const bool rows = 16 * wave < nx;  // the wave has rows of P
-        double xb[kKS];
-#pragma unroll
-        for (int ks = 0; ks < kKS; ++ks) {
-            const int x = 4 * ks + lk;
-            xb[ks] = (i < nx && x < r0) ? Xx[(int64_t)i * kFitR + x] : 0.0;
-        }
-        float *Pb = ctrl + b.ctrl_off;
-        const int k1 = min(nz, k0 + kgroup);
-        const int nq = (ny + 15) >> 4;
-        // slice k in registers: element e = tid + kFitThreads m of the r0 x r1 slice
-        double sv[kSliceRegs];
-        auto fetch = [&](int k) {
-            const double *Tk = T + ((int64_t)bi * max_n + k) * lines;
-#pragma unroll
-            for (int m = 0; m < kSliceRegs; ++m) {
-                const int e = tid + kFitThreads * m;
-                sv[m] = (k < k1 && e < lines) ? Tk[e] : 0.0;
-            }
-        };
-        fetch(k0);
-        for (int k = k0; k < k1; ++k) {
-#pragma unroll
-            for (int m = 0; m < kSliceRegs; ++m) {
-                const int e = tid + kFitThreads * m;
-                if (e < lines) {
-                    const int x = e / r1;
-                    sm.S[x][e - x * r1] = sv[m];
-                }
-            }
-            __syncthreads();
-            fetch(k + 1);  // in flight during this slice's products
-            if (rows) {
-                if (nq >= 4) fit_xy_slice<4>(sm, wave, lr, lk, r0, r1, nx, ny, nz, k, xb, Pb);
-                else if (nq == 3) fit_xy_slice<3>(sm, wave, lr, lk, r0, r1, nx, ny, nz, k, xb, Pb);
-                else if (nq == 2) fit_xy_slice<2>(sm, wave, lr, lk, r0, r1, nx, ny, nz, k, xb, Pb);
-                else fit_xy_slice<1>(sm, wave, lr, lk, r0, r1, nx, ny, nz, k, xb, Pb);
-            }
-            __syncthreads();
-        }
+    const int tid = threadIdx.x;
+    const int groups = (a.r0 + xgroup - 1) / xgroup;
+    const int bi = (int)(blockIdx.x / groups);
+    const int x0 = (int)(blockIdx.x - (int64_t)bi * groups) * xgroup;
+    const int x1 = min(a.r0, x0 + xgroup);
+    const fa_block &b = a.blocks[bi];
+    const int ny = uni32(b.ncp[1]), nz = uni32(b.ncp[2]);
+    // the workspace has no room for it (the lattice is left as is), or the
+    // Gram matrix is singular (fit_x_kernel writes the lattice)
+    if (nz > a.max_n || ny > a.r1) return;
+    const int nk = (nz + 15) >> 4, nj = (ny + 15) >> 4;
+    double *oz = reinterpret_cast<double *>(smem_raw), *oy = oz + nk * kOpTile;
+    const double *X = fit_x_of(a, bi);
+    // X_z[k][z] to the z product's B operand (step (q, j), lane), X_y[j][y]
+    // to the y product's A operand (step (t, r), lane); zero outside
+    for (int e = tid; e < (nk + nj) * kOpTile; e += kZyWaves * 64) {
+        const bool isz = e < nk * kOpTile;
+        const int f = isz ? e : e - nk * kOpTile;
+        const int step = (f >> 6) & (kOpSteps - 1), g = (f >> 4) & 3;
+        const int row = (f / kOpTile) * 16 + (f & 15);
+        const int c = isz ? 16 * (step >> 2) + 4 * g + (step & 3) : 4 * step + g;
+        const bool in = isz ? (row < nz && c < a.r2) : (row < ny && c < a.r1);
+        oz[e] = in ? X[(isz ? 2 : 1) * kPinvStride + row * kFitR + c] : 0.0;
     }
+    __syncthreads();
+    if (nj == 4) fit_zy_block<NT, 4>(a, bi, x0, x1, ny, nz, oz, oy);
+    else if (nj == 3) fit_zy_block<NT, 3>(a, bi, x0, x1, ny, nz, oz, oy);
+    else if (nj == 2) fit_zy_block<NT, 2>(a, bi, x0, x1, ny, nz, oz, oy);
+    else fit_zy_block<NT, 1>(a, bi, x0, x1, ny, nz, oz, oy);
+}
+
+// P[i][e] = sum_x X_x[i][x] U[x][e], e = j n_z + k: the lattice is
+// contiguous in e, so both sides stream.  A wave takes 16-wide tiles of e and
+// all of i; the next tile's U is in flight during a tile's products.  Bound by
+// the stream of U (512 blocks of 32^3: 335 MB in 108 us); 32-wide tiles (two
+// columns per lane, half the waves) took 118 us.
+constexpr int kFxWaves = 4;
+
+template <int NI>
+__device__ __forceinline__ void fit_x_tiles(const FitArgs &a, int t0, int t1, int nx, int ne,
+                                            const double *U, const double *ox, float *P) {
+    const int wave = uni32(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int gq = lane >> 4, l16 = lane & 15;
+    // rows x >= r0 and i >= n_x lie past the resources' ends, tiles past the
+    // last at a dead offset: the loop issues the same accesses every time
+    const uint32_t ub = (uint32_t)ne * 8u, pb = (uint32_t)ne * 4u;
+    const __amdgpu_buffer_rsrc_t ur = make_rsrc(U, (uint32_t)a.r0 * ub);
+    const __amdgpu_buffer_rsrc_t pr = make_rsrc(P, (uint32_t)nx * pb);
+    auto load = [&](int t, double(&u)[kOpSteps]) {
+        const int e = 16 * t + l16;
+        const uint32_t at = t < t1 && e < ne ? (uint32_t)gq * ub + (uint32_t)e * 8u : kDeadFit;
+#pragma unroll
+        for (int ks = 0; ks < kOpSteps; ++ks)
+            u[ks] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                                   ur, at, (uint32_t)(4 * ks) * ub, 0));
+    };
+    double cur[kOpSteps], nxt[kOpSteps];
+    int t = t0 + wave;
+    load(t, cur);
+    for (; t < t1; t += kFxWaves) {
+        load(t + kFxWaves, nxt);
+        int ol = lane;
+        asm volatile("" : "+v"(ol));  // the operands stay in LDS from tile to tile
+        f64x4 acc[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int ks = 0; ks < kOpSteps; ++ks)
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+                acc[i] = mfma64(ox[i * kOpTile + ks * kWave + ol], cur[ks], acc[i]);
+        const int e = 16 * t + l16;
+        const uint32_t at = e < ne ? (uint32_t)gq * pb + (uint32_t)e * 4u : kDeadFit;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)acc[i][r]), pr, at,
+                                                      (uint32_t)(16 * i + 4 * r) * pb, 0);
+#pragma unroll
+        for (int ks = 0; ks < kOpSteps; ++ks) cur[ks] = nxt[ks];
+    }
+}
+
+__global__ __launch_bounds__(kFxWaves * 64) void fit_x_kernel(FitArgs a, int echunks, int tchunk) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int tid = threadIdx.x;
+    const int bi = (int)(blockIdx.x / echunks);
+    const int t0 = (int)(blockIdx.x - (int64_t)bi * echunks) * tchunk;
+    const fa_block &b = a.blocks[bi];
+    const int nx = uni32(b.ncp[0]), ny = uni32(b.ncp[1]), nz = uni32(b.ncp[2]);
+    const int ne = ny * nz, t1 = min(t0 + tchunk, (ne + 15) >> 4);
+    if (nz > a.max_n || t0 >= t1) return;
+    float *P = a.ctrl + b.ctrl_off;
+    if (ny > a.r1) {  // more functions than samples: no least-squares lattice
+        for (int64_t e = tid; e < (int64_t)nx * ne; e += kFxWaves * 64) P[e] = __builtin_nanf("");
+        return;
+    }
+    double *ox = reinterpret_cast<double *>(smem_raw);
+    const double *X = fit_x_of(a, bi);
+    const int ni = (nx + 15) >> 4;
+    for (int f = tid; f < ni * kOpTile; f += kFxWaves * 64) {
+        const int c = 4 * ((f >> 6) & (kOpSteps - 1)) + ((f >> 4) & 3);
+        const int row = (f / kOpTile) * 16 + (f & 15);
+        ox[f] = (row < nx && c < a.r0) ? X[row * kFitR + c] : 0.0;
+    }
+    __syncthreads();
+    const double *U = a.T + (int64_t)bi * a.tstride;
+    if (ni == 4) fit_x_tiles<4>(a, t0, t1, nx, ne, U, ox, P);
+    else if (ni == 3) fit_x_tiles<3>(a, t0, t1, nx, ne, U, ox, P);
+    else if (ni == 2) fit_x_tiles<2>(a, t0, t1, nx, ne, U, ox, P);
+    else fit_x_tiles<1>(a, t0, t1, nx, ne, U, ox, P);
 }
 
 // errs[b * stride + 0] = max |y - f|, errs[b * stride + 1] = sqrt(mean (y-f)^2).
@@ -557,23 +595,23 @@ __global__ __launch_bounds__(kFitThreads) void mse_grad_kernel(const float *f, c
     }
 }
 
-// Descriptors and shared knots of one candidate NCP (same n and p on every
-// axis, clamped uniform knots t_{p+j} = j / (n - p)); lattices at `cstride`.
-__global__ void candidate_kernel(fa_block *desc, float *knots, int nblocks, int n, int p,
-                                 int64_t cstride) {
+// Descriptors of `ncand` candidate NCPs n = n0, n0 - 1, ... of a search (same
+// n and p on every axis, knots of n at (n - ncp_lo) * kstride): entry c *
+// nblocks + b, its lattice at (c % g * nblocks + b) * cstride (g candidates
+// are fitted at a time).
+__global__ void candidate_kernel(fa_block *desc, int nblocks, int ncand, int n0, int ncp_lo, int p,
+                                 int g, int kstride, int64_t cstride) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nk = n + p + 1;
-    if (i < 3 * nk) knots[i] = candidate_knot(i % nk, n, p);
-    if (i < nblocks) {
-        fa_block d{};
-        d.ncp[0] = d.ncp[1] = d.ncp[2] = n;
-        d.degree[0] = d.degree[1] = d.degree[2] = p;
-        d.knot_off = 0;
-        d.ctrl_off = (int64_t)i * cstride;
-        d.scale = 1.0f;
-        d.flags = FA_FLAG_UNIFORM_X | FA_FLAG_UNIFORM_Y | FA_FLAG_UNIFORM_Z;
-        desc[i] = d;
-    }
+    if (i >= nblocks * ncand) return;
+    const int c = i / nblocks, n = n0 - c;
+    fa_block d{};
+    d.ncp[0] = d.ncp[1] = d.ncp[2] = n;
+    d.degree[0] = d.degree[1] = d.degree[2] = p;
+    d.knot_off = (int64_t)(n - ncp_lo) * kstride;
+    d.ctrl_off = (int64_t)(c % g * nblocks + i % nblocks) * cstride;
+    d.scale = 1.0f;
+    d.flags = FA_FLAG_UNIFORM_X | FA_FLAG_UNIFORM_Y | FA_FLAG_UNIFORM_Z;
+    desc[i] = d;
 }
 
 }  // namespace
@@ -587,14 +625,17 @@ namespace {
 // raise the dynamic LDS limits of the fit kernels once per process
 hipError_t fit_attributes() {
     static const hipError_t attr = [] {
-        const void *ks[4] = {reinterpret_cast<const void *>(&fit_z_kernel),
-                             reinterpret_cast<const void *>(&fit_xy_kernel),
+        const void *ks[7] = {reinterpret_cast<const void *>(&fit_zy_kernel<1>),
+                             reinterpret_cast<const void *>(&fit_zy_kernel<2>),
+                             reinterpret_cast<const void *>(&fit_zy_kernel<3>),
+                             reinterpret_cast<const void *>(&fit_zy_kernel<4>),
+                             reinterpret_cast<const void *>(&fit_x_kernel),
                              reinterpret_cast<const void *>(&fit_pinv_kernel),
                              reinterpret_cast<const void *>(&pinv_candidates_kernel)};
-        const int bytes[4] = {(int)sizeof(FitZSmem), (int)sizeof(FitXYSmem),
-                              (int)sizeof(PinvSmem), (int)sizeof(PinvSmem)};
+        const int zy = 8 * kOpTile * (int)sizeof(double);
+        const int bytes[7] = {zy, zy, zy, zy, zy / 2, (int)sizeof(PinvSmem), (int)sizeof(PinvSmem)};
         hipError_t r = hipSuccess;
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < 7; ++i) {
             const hipError_t e =
                 hipFuncSetAttribute(ks[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
             if (e != hipSuccess) r = e;
@@ -604,25 +645,31 @@ hipError_t fit_attributes() {
     return attr;
 }
 
-// the two products of a fit given the pseudo-inverses: block b's X_a at
-// X + b * xstride + a * kPinvStride
-hipError_t launch_fit_products(const fa_block *blocks, int nblocks, const float *knots, int rx,
-                               int ry, int rz, int max_n, const float *samples, double *T,
-                               const double *X, int64_t xstride, float *ctrl, hipStream_t s) {
-    const int64_t chunks = ((int64_t)rx * ry + kZLines - 1) / kZLines;
-    // chunks per workgroup: as many as leave about 512 workgroups (two per CU)
-    const int cgroup =
-        (int)std::max<int64_t>(1, std::min<int64_t>(chunks, (int64_t)nblocks * chunks / 512));
-    const int64_t zitems = (int64_t)nblocks * ((chunks + cgroup - 1) / cgroup);
-    const int gz = (int)std::min<int64_t>(zitems, 65536);
-    hipLaunchKernelGGL(fit_z_kernel, dim3(gz), dim3(kFitThreads), sizeof(FitZSmem), s, blocks,
-                       nblocks, knots, rx, ry, rz, max_n, cgroup, samples, X, xstride, T);
-    // k values per workgroup: as many as keep about 2048 workgroups busy
-    const int kgroup = (int)std::max<int64_t>(1, std::min<int64_t>(max_n, (int64_t)nblocks * max_n / 2048));
-    const int64_t groups = (max_n + kgroup - 1) / kgroup;
-    const int gxy = (int)std::min<int64_t>((int64_t)nblocks * groups, 65536);
-    hipLaunchKernelGGL(fit_xy_kernel, dim3(gxy), dim3(kFitThreads), sizeof(FitXYSmem), s, blocks,
-                       nblocks, knots, rx, ry, max_n, kgroup, X, xstride, T, ctrl);
+// the two products of a fit given the pseudo-inverses; max_y >= NCP_y of
+// every entry that has no more functions than samples along y
+hipError_t launch_fit_products(const FitArgs &a, int max_y, hipStream_t s) {
+    // slices per workgroup (a multiple of its waves): as many as leave two
+    // workgroups per CU, both resident (one's set-up hides behind the other's
+    // products)
+    const int64_t rounds = (int64_t)a.nblocks * ((a.r0 + kZyWaves - 1) / kZyWaves);
+    const int xgroup = kZyWaves * (int)std::max<int64_t>(1, std::min<int64_t>(16, rounds / 512));
+    const int64_t groups = (a.r0 + xgroup - 1) / xgroup;
+    const int nk = (a.max_n + 15) / 16, nj = (std::min(max_y, a.r1) + 15) / 16;
+    const size_t lds = (size_t)(nk + nj) * kOpTile * sizeof(double);
+    const dim3 gz((unsigned)(a.nblocks * groups)), tz(kZyWaves * 64);
+    switch ((a.r1 + 15) / 16) {
+    case 1: hipLaunchKernelGGL(fit_zy_kernel<1>, gz, tz, lds, s, a, xgroup); break;
+    case 2: hipLaunchKernelGGL(fit_zy_kernel<2>, gz, tz, lds, s, a, xgroup); break;
+    case 3: hipLaunchKernelGGL(fit_zy_kernel<3>, gz, tz, lds, s, a, xgroup); break;
+    default: hipLaunchKernelGGL(fit_zy_kernel<4>, gz, tz, lds, s, a, xgroup); break;
+    }
+    // tiles per workgroup: as many as leave eight workgroups per CU
+    const int tiles = (std::min(max_y, a.r1) * a.max_n + 15) / 16;
+    const int64_t quads = (int64_t)a.nblocks * ((tiles + kFxWaves - 1) / kFxWaves);
+    const int tchunk = kFxWaves * (int)std::max<int64_t>(1, std::min<int64_t>(8, quads / 2048));
+    const int echunks = (tiles + tchunk - 1) / tchunk;
+    hipLaunchKernelGGL(fit_x_kernel, dim3((unsigned)((int64_t)a.nblocks * echunks)),
+                       dim3(kFxWaves * 64), 4 * kOpTile * sizeof(double), s, a, echunks, tchunk);
     return hipGetLastError();
 }
 }  // namespace
@@ -633,11 +680,12 @@ hipError_t launch_fit(const fa_block *blocks, int nblocks, const float *knots, i
     const hipError_t attr = fit_attributes();
     if (attr != hipSuccess) return attr;
     double *Xg = T + (int64_t)nblocks * max_n * rx * ry;
-    const int gp = (int)std::min<int64_t>((int64_t)nblocks * 3, 65536);
-    hipLaunchKernelGGL(fit_pinv_kernel, dim3(gp), dim3(kFitThreads), sizeof(PinvSmem), s, blocks,
+    const int gp = (int)std::min<int64_t>((int64_t)nblocks * 3, 1 << 20);
+    hipLaunchKernelGGL(fit_pinv_kernel, dim3(gp), dim3(kWave), sizeof(PinvSmem), s, blocks,
                        nblocks, knots, rx, ry, rz, Xg);
-    return launch_fit_products(blocks, nblocks, knots, rx, ry, rz, max_n, samples, T, Xg,
-                               3 * kPinvStride, ctrl, s);
+    const FitArgs a{blocks, nblocks, nblocks, rx, ry, rz, max_n, samples, Xg, 0, 3 * kPinvStride,
+                    T, (int64_t)max_n * rx * ry, ctrl};
+    return launch_fit_products(a, kFitN, s);
 }
 
 int64_t pinv_doubles() { return kPinvStride; }
@@ -646,19 +694,19 @@ hipError_t launch_pinv_candidates(float *kall, int ncp_lo, int ncand, int p, int
                                   int ry, int rz, double *xall, hipStream_t s) {
     const hipError_t attr = fit_attributes();
     if (attr != hipSuccess) return attr;
-    const int grid = std::min(ncand * 3, 65536);
-    hipLaunchKernelGGL(pinv_candidates_kernel, dim3(grid), dim3(kFitThreads), sizeof(PinvSmem), s,
+    hipLaunchKernelGGL(pinv_candidates_kernel, dim3(ncand * 3), dim3(kWave), sizeof(PinvSmem), s,
                        kall, ncp_lo, ncand, p, kstride, rx, ry, rz, xall);
     return hipGetLastError();
 }
 
-hipError_t launch_fit_shared(const fa_block *blocks, int nblocks, const float *knots, int rx,
-                             int ry, int rz, int max_n, const float *samples, double *T,
-                             const double *X, float *ctrl, hipStream_t s) {
+hipError_t launch_fit_candidates(const fa_block *desc, int nblocks, int ncand, int rx, int ry,
+                                 int rz, int max_n, const float *samples, const double *X,
+                                 double *T, float *ctrl, hipStream_t s) {
     const hipError_t attr = fit_attributes();
     if (attr != hipSuccess) return attr;
-    return launch_fit_products(blocks, nblocks, knots, rx, ry, rz, max_n, samples, T, X, 0, ctrl,
-                               s);
+    const FitArgs a{desc, nblocks * ncand, nblocks, rx, ry, rz, max_n, samples, X,
+                    -3 * kPinvStride, 0, T, (int64_t)rx * max_n * max_n, ctrl};
+    return launch_fit_products(a, max_n, s);
 }
 
 hipError_t launch_residual(const float *y, const float *f, int64_t vox, int nblocks, float *errs,
@@ -682,11 +730,10 @@ hipError_t launch_mse_grad(const float *f, const float *y, int64_t vox, int nblo
     return hipGetLastError();
 }
 
-hipError_t launch_candidate(fa_block *desc, float *knots, int nblocks, int n, int p,
-                            int64_t cstride, hipStream_t s) {
-    const int cnt = nblocks > 3 * (n + p + 1) ? nblocks : 3 * (n + p + 1);
-    hipLaunchKernelGGL(candidate_kernel, dim3((cnt + 255) / 256), dim3(256), 0, s, desc, knots,
-                       nblocks, n, p, cstride);
+hipError_t launch_candidates(fa_block *desc, int nblocks, int ncand, int n0, int ncp_lo, int p, int g,
+                             int kstride, int64_t cstride, hipStream_t s) {
+    hipLaunchKernelGGL(candidate_kernel, dim3((nblocks * ncand + 255) / 256), dim3(256), 0, s, desc,
+                       nblocks, ncand, n0, ncp_lo, p, g, kstride, cstride);
     return hipGetLastError();
 }
 

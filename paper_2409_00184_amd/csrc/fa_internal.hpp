@@ -38,8 +38,8 @@ struct DecodeLaunch {
     double *partials;
     // error form (samples set, errs set, nothing stored per voxel): per-item
     // max |f - samples| and FP64 sum of squares into partials[2 item + {0,1}]
-    float *errs;
-    int64_t errs_stride;
+    int error_form;
+    int nsrc;                // entry e reads the samples of block e % nsrc
     // decode form: all four channels stored as one 16-byte record per voxel,
     // out = [block][u][v][w][4]
     int interleave;
@@ -50,10 +50,11 @@ hipError_t launch_decode_mfma(const DecodeLaunch &a, int waves, int grid, hipStr
 // per-block sums of the per-item partials of the residual decode
 hipError_t launch_residual_combine(const double *partials, int nblocks, int per, double *sumsq,
                                    hipStream_t s);
-// errs[b * stride + {0, 1}] = (max, rms) of block b from the error form's
-// per-item partials, items in order
-hipError_t launch_errors_combine(const double *partials, int nblocks, int per, int64_t vox,
-                                 float *errs, int64_t stride, hipStream_t s);
+// errs[b * stride - 2 c + {0, 1}] = (max, rms) of block b under candidate c <
+// ncand (entry c * nblocks + b) from the error form's per-item partials, items
+// in order
+hipError_t launch_errors_combine(const double *partials, int nblocks, int ncand, int per,
+                                 int64_t vox, float *errs, int64_t stride, hipStream_t s);
 hipError_t launch_decode_plain(const fa_block *blocks, int nblocks, const float *knots,
                                const float *ctrl, int rx, int ry, int rz, uint32_t mask,
                                float *out, hipStream_t s);
@@ -101,19 +102,24 @@ hipError_t launch_residual(const float *y, const float *f, int64_t vox, int nblo
                            int64_t stride, hipStream_t s, int chunks = 1, double *part = nullptr);
 hipError_t launch_mse_grad(const float *f, const float *y, int64_t vox, int nblocks, float scale,
                            float *grad, double *sumsq, hipStream_t s);
-hipError_t launch_candidate(fa_block *desc, float *knots, int nblocks, int n, int p,
-                            int64_t cstride, hipStream_t s);
+// descriptors of `ncand` candidates n0, n0 - 1, ... of a search (entry c *
+// nblocks + b; lattices of g candidates at a time, `cstride` floats each)
+hipError_t launch_candidates(fa_block *desc, int nblocks, int ncand, int n0, int ncp_lo, int p, int g,
+                             int kstride, int64_t cstride, hipStream_t s);
 // doubles of one (block or candidate, axis) pseudo-inverse
 int64_t pinv_doubles();
 // knots and per-axis pseudo-inverses of every candidate NCP ncp_lo + c,
 // c < ncand, of a search (clamped uniform knots shared by all blocks):
-// knots at kall + c * kstride, X_a at xall + (3 c + a) * pinv_doubles()
+// knots at kall + c * kstride (x, y, z vectors back to back), X_a at xall +
+// (3 c + a) * pinv_doubles()
 hipError_t launch_pinv_candidates(float *kall, int ncp_lo, int ncand, int p, int kstride, int rx,
                                   int ry, int rz, double *xall, hipStream_t s);
-// launch_fit with one set of pseudo-inverses X (3 axes) shared by every block
-hipError_t launch_fit_shared(const fa_block *blocks, int nblocks, const float *knots, int rx,
-                             int ry, int rz, int max_n, const float *samples, double *T,
-                             const double *X, float *ctrl, hipStream_t s);
+// the lattices of `ncand` candidates of descending NCP (largest max_n) on the
+// same nblocks blocks of samples; X: pseudo-inverses of the first, the next
+// candidate's 3 pinv_doubles() before it; T: rx * max_n^2 doubles per entry
+hipError_t launch_fit_candidates(const fa_block *desc, int nblocks, int ncand, int rx, int ry,
+                                 int rz, int max_n, const float *samples, const double *X,
+                                 double *T, float *ctrl, hipStream_t s);
 
 // One block of a staging gather: its slot in the mapped host cache, where
 // its knots and lattice go in the device batch, and its descriptor.
