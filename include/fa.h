@@ -286,19 +286,17 @@ fa_status fa_render_rays(const fa_block *blocks, int32_t nblocks, const int32_t 
  * fit of the lattice to samples y on the block's grid, this is the fit's
  * gradient: the step model(NCP, degree) of Alg. 1 (Sec. 4.2.1) solves that
  * fit for every candidate NCP.  Deterministic (fixed summation order, no
- * floating-point atomics).  A value-only cotangent (mask 1) whose rows start
- * on 16-byte boundaries (res[2] a multiple of 4, grad_out 16-byte aligned)
- * runs on the FP32 matrix cores; other cotangents run on the VALU.
+ * floating-point atomics).  Runs on the FP32 matrix cores, whose products
+ * include zero weights: an infinite or NaN cotangent value makes the
+ * gradient of its whole block NaN, not only that of its window.
  *   grad_out   device FP32 [nblocks][popcount(mask)][res0][res1][res2]
  *   grad_ctrl  device FP32 lattice layout (same offsets as ctrl); the
  *              lattices of the blocks are overwritten, other elements are
  *              left untouched
- * res[1] and res[2] (the y and z resolutions) must be at most 64: one
- * workgroup streams each block's cotangent one x slice at a time, the
- * matrix-core form holding a slice's y and z extent as four 16-row bands of
- * four 16-column groups in registers, the VALU form holding the slice, its
- * z-contracted form and the dense y and z basis matrices in LDS
- * (FA_ERR_UNSUPPORTED above 64; res[0] takes up to FA_MAX_RES).
+ * res[1] and res[2] (the y and z resolutions) must be at most 64: a wave
+ * holds an x slice's y and z extent as four 16-row bands of four 16-column
+ * groups in registers (FA_ERR_UNSUPPORTED above 64; res[0] takes up to
+ * FA_MAX_RES).
  */
 fa_status fa_decode_backward(const fa_block *blocks, int32_t nblocks, const float *knots,
                              const int32_t res[3], uint32_t mask, const float *grad_out,
@@ -473,6 +471,12 @@ fa_status fa_decode_residual_noalloc(const fa_block *blocks, int32_t nblocks,
 int64_t fa_ncp_search_workspace(int32_t nblocks, const int32_t res[3], int32_t degree,
                                 int32_t ncp_hi);
 
+/* Bytes with which fa_ncp_search fits several NCPs per launch instead of one
+ * (the same error map; faster where nblocks is small).  Never below
+ * fa_ncp_search_workspace; -1 for invalid sizes. */
+int64_t fa_ncp_search_workspace_wide(int32_t nblocks, const int32_t res[3], int32_t degree,
+                                     int32_t ncp_hi);
+
 /*
  * In-level exhaustive search of Sec. 4.2.1 (the inner loop of Alg. 1): for
  * every NCP n from ncp_hi down to ncp_lo, every block is fitted with n
@@ -485,6 +489,7 @@ int64_t fa_ncp_search_workspace(int32_t nblocks, const int32_t res[3], int32_t d
  * a fixed order, so the map is deterministic.
  *   samples    device FP32 [nblocks][res0][res1][res2]
  *   workspace  device, >= fa_ncp_search_workspace(...) bytes, 256-B aligned
+ *              (with fa_ncp_search_workspace_wide(...) bytes the call is faster)
  * Requires degree + 1 <= ncp_lo <= ncp_hi <= min(res) (FA_ERR_INVALID_ARG
  * otherwise); degree > 3, ncp_hi > FA_MAX_NCP or res > 64 on any axis give
  * FA_ERR_UNSUPPORTED.  Asynchronous on `stream`; no allocation.

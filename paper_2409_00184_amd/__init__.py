@@ -125,6 +125,8 @@ def _load():
     L.fa_model_errors.argtypes = [vp, i32, vp, vp, ctypes.c_int, vp, vp, vp, vp, i64, vp]
     L.fa_ncp_search_workspace.restype = i64
     L.fa_ncp_search_workspace.argtypes = [i32, vp, i32, i32]
+    L.fa_ncp_search_workspace_wide.restype = i64
+    L.fa_ncp_search_workspace_wide.argtypes = [i32, vp, i32, i32]
     L.fa_ncp_search.restype = ctypes.c_int
     L.fa_ncp_search.argtypes = [vp, i32, vp, i32, i32, i32, vp, vp, i64, vp]
     L.fa_ncp_select.restype = ctypes.c_int
@@ -485,7 +487,11 @@ def ncp_search(samples, degree, ncp_lo=None, ncp_hi=None, workspace=None, stream
     if need < 0:
         raise FAError("fa_ncp_search_workspace", FA_ERR_INVALID_ARG)
     if workspace is None or workspace.numel() < need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=samples.device)
+        wide = lib.fa_ncp_search_workspace_wide(nb, _i32x3(res), int(degree), hi)
+        try:  # several NCPs per launch where memory allows, else one
+            workspace = torch.empty(wide, dtype=torch.uint8, device=samples.device)
+        except torch.OutOfMemoryError:
+            workspace = torch.empty(need, dtype=torch.uint8, device=samples.device)
     errs = torch.empty((nb, hi - lo + 1, 2), dtype=torch.float32, device=samples.device)
     st = lib.fa_ncp_search(_ptr(samples), nb, _i32x3(res), int(degree), lo, hi, _ptr(errs),
                            _ptr(workspace), workspace.numel(), _stream(stream))

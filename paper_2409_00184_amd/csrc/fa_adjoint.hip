@@ -1,291 +1,669 @@
-// Adjoint of the grid decode on gfx950 (row a7): G = B^T g.
+// Adjoint of the grid decode on the FP32 matrix cores (row a7): G = B^T g.
+// With a cotangent of the values alone it is the least-squares fit's
+// gradient (2/M) B^T r that the fit of control points needs; with cotangents
+// of the derivative channels, that of a loss on gradients too.
 //
-// The fit of control points to samples (the least-squares model(NCP,
-// degree) that Alg. 1 runs for each candidate NCP) has gradient
-// (2/M) B^T r.  B^T is the transposed separable contraction:
-//   HB[i][v][w] = sum_u Bx[u][i] g0 + Dx[u][i] g1,  H2, H3 = sum_u Bx[u][i] g2, g3
-//   KB[i][j][w] = sum_v By[v][j] HB + Dy[v][j] H2,  K3 = sum_v By[v][j] H3
-//   G[i][j][k]  = sum_w Bz[w][k] KB + Dz[w][k] K3
-// One workgroup (16 waves) per micro-model streams its cotangent block once:
-// lanes own z columns, wave q owns y rows q, q+16, ...; walking x, every
-// lane keeps the p+1 newest partial x contractions of its columns in
-// registers (the transpose of the forward decode's sliding window).  When
-// control plane i leaves the window it is final: the workgroup writes
-// HB/H2/H3 of that plane to LDS, contracts y over each j's contiguous v
-// support, then z over each k's w support, and stores the plane of G once.
-// Fixed summation order, no atomics: the result is deterministic.
+// The transposed tensor-product contraction is ordered per x slice u of the
+// cotangent block; for the values
+//     Z_u[v][k] = sum_w g[u][v][w] Bz[w][k]        (z, dense product)
+//     Y_u[j][k] = sum_v By[v][j] Z_u[v][k]         (y, dense product)
+//     G[i][j][k] += Bx[u][i] Y_u[j][k]             (x, p+1 planes per slice)
+// and with all four channels
+//     Z0 = g_0 Bz + g_3 Dz,  Z1 = g_1 Bz,  Z2 = g_2 Bz
+//     G[i] += Bx[u][i] (By^T Z0 + Dy^T Z2) + Dx[u][i] By^T Z1.
+// The products run on v_mfma_f32_16x16x4f32 and never leave the wave's
+// registers: the z product of a 16-row band of the slice leaves its 16 x 16
+// tile of Z_u in exactly the operand layout of four K steps of the y
+// product, so a wave contracts its slices from HBM to Y_u without LDS or
+// barriers.  A wave owns one 16-wide k tile and up to two 16-wide j tiles
+// of the output and a chunk of consecutive x slices; it keeps the p+1
+// control planes its current slice touches in a register ring (plane i in
+// slot i mod (p+1)) and stores a plane once when the span along x moves
+// past it.  The waves of a workgroup split its x slices into chunks
+// whose plane ranges overlap only with their neighbours' (at most p+1
+// planes per boundary): the chunk to the right of a boundary leaves its
+// partial planes there in LDS, and the chunk to the left adds them to its
+// own after the workgroup's one barrier.  The z product's K steps cover the
+// 16-column groups of w inside the basis band of the wave's k tile; the y
+// product runs over all four row bands (its y basis operands are zero
+// outside each j tile's band).  The slice body is straight-line code, one
+// instance per (band width, one or two j tiles), so that the four z chains
+// (one per row band), the loads of the next slice and the y chains of a
+// slice are scheduled together.  Fixed summation order, no floating-point
+// atomics: the result is deterministic.
 //
-// This form serves cotangents with derivative channels; a value-only
-// cotangent (the fit's residual) goes to the matrix-core form of
-// fa_adjoint_mfma.hip.  The kernel can also split a micro-model's control
-// planes between segments: a segment owns planes [i0, i1), streams exactly
-// the x positions whose basis touches them (neighbouring segments re-read
-// the p-plane overlap) and stores only its own planes, so every plane is
-// still written by one workgroup.
+// Values only: the basis operands of both products stay in registers for
+// the whole block.  All channels: they sit in LDS in lane order (16 reads of
+// 1 KB per channel and slice against 64 products), and two buffers hold the
+// channel in use and the one in flight.
+//
+// A micro-model is split between `nseg` workgroups when there are fewer
+// micro-models than CUs: a segment owns the control planes [i0, i1), streams
+// the slices whose basis touches them (neighbours re-read an overlap of p
+// spans) and stores its own planes only.
+//
+// Bound by the matrix cores of the busiest SIMD and the cotangent's reads:
+// values of 256 blocks of 64^3, NCP 16..32, 84 us (3.2 TB/s); all channels of
+// 128 blocks, NCP 8..32, 195 us (2.8 TB/s), where a form on the vector ALUs,
+// one workgroup per block with three barriers per control plane, took 914.
+//
+// Operand layout of v_mfma_f32_16x16x4f32 (checked on the device): lane l
+// holds A[l%16][l/16] and B[l/16][l%16] and receives D[4(l/16)+r][l%16].
+// The z product sums w in the order w = 16 q + 4 (l/16) + j (step (q, j)),
+// so each lane reads four consecutive w of its row with one 16-byte load;
+// the y product sums v = 16 m + 4 (l/16) + r (step (m, r)), which is the
+// row that lane's result register r of band m's Z tile holds.
 #include "fa_device.hpp"
 #include "fa_internal.hpp"
+
+#include <algorithm>
+#include <type_traits>
 
 namespace fa {
 namespace {
 
-constexpr int kAdjMaxYZ = 64;                      // res[1], res[2] limit
-constexpr int kPlane = kAdjMaxYZ * kWave;          // one (v, w) plane
+typedef float f32x4a __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// waves per workgroup: 16 with derivative cotangents, 8 for value only
-template <bool DER>
-constexpr int adj_waves() { return DER ? 16 : 8; }
+constexpr int kAW = 8;           // waves per workgroup
+constexpr int kAT = kAW * 64;    // threads per workgroup
+constexpr int kAM = 64;          // res[1], res[2] and NCP_y, NCP_z limit
+constexpr int kJT = 2;           // j tiles per wave
+constexpr int kCUs = 256;
+constexpr int kMaxSegs = 8;      // segments of a micro-model
+// partial planes of the chunk boundaries: at most (X - 1) (p + 1) NCP_y
+// NCP_z floats, X <= kAW / (k tiles x j tile pairs), which is below
+// (p + 1) * 4096 for every shape
+constexpr int kLB = 4 * 4096;
 
 template <bool DER>
-struct AdjSmem {
-    float4 xB[kMaxRes], xD[kMaxRes];
-    int xS[kMaxRes];
-    float4 yB[kAdjMaxYZ], yD[kAdjMaxYZ];
-    int yS[kAdjMaxYZ];
-    float4 zB[kAdjMaxYZ], zD[kAdjMaxYZ];
-    int zS[kAdjMaxYZ];
-    int jva[FA_MAX_NCP], jvb[FA_MAX_NCP];  // v support of control row j
-    int kwa[FA_MAX_NCP], kwb[FA_MAX_NCP];  // w support of control column k
+struct AmSmem;
+
+template <>
+struct AmSmem<false> {
     float kn[kMaxKnotsPerBlock + 4];
-    float H[DER ? 3 : 1][kPlane];          // HB, H2, H3 of the plane being emitted
-    float K[DER ? 2 : 1][FA_MAX_NCP * kWave];  // KB, K3
+    float4 xB[kMaxRes];  // x basis of each slice in ring order
+    int xS[kMaxRes];     // span along x of each slice
+    float4 yN[kAM];      // y basis of each v (entries beyond p zero)
+    float4 zN[kAM];
+    int ys[kAM];         // span along y of each v
+    int zs[kAM];
+    int tw[2][kAM / 16];  // first and last w with a basis entry in each k tile
+    float lb[kLB];        // left partial planes of chunks 1..X-1
 };
 
-__device__ __forceinline__ float comp4(const float4 &v, int r) {
-    return r == 0 ? v.x : (r == 1 ? v.y : (r == 2 ? v.z : v.w));
+template <>
+struct AmSmem<true> : AmSmem<false> {
+    float4 xD[kMaxRes], yD[kAM], zD[kAM];  // derivatives beside xB, yN, zN
+    // operands in lane order, basis then derivative: the z product's of k
+    // tile t and columns 16q + 4(l/16) + (x, y, z, w), the y product's of j
+    // tile t and rows 16m + 4(l/16) + (x, y, z, w)
+    float4 zop[2][kAM / 16][4][kWave], yop[2][kAM / 16][4][kWave];
+};
+
+__device__ __forceinline__ f32x4a mma4(float a, float b, const f32x4a &c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ float pick4(const float4 &v, int d) {
+    return d == 0 ? v.x : (d == 1 ? v.y : (d == 2 ? v.z : v.w));
 }
 
 template <int P>
-__device__ __forceinline__ void tab_axis(const float *t, int n, int R, int idx, float4 &b4,
-                                         float4 &d4, int &s) {
-    const float pos = grid_pos(idx, R);
-    s = span_search(n, P, t, pos);
-    float N[P + 1], D[P + 1];
-    basis_ders<P>(t, s, pos, N, D);
-    float nb[4] = {0, 0, 0, 0}, nd[4] = {0, 0, 0, 0};
+__device__ __forceinline__ float4 row4(const float (&v)[P + 1]) {
+    float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int r = 0; r <= P; ++r) {
-        nb[r] = N[r];
-        nd[r] = D[r];
-    }
-    b4 = make_float4(nb[0], nb[1], nb[2], nb[3]);
-    d4 = make_float4(nd[0], nd[1], nd[2], nd[3]);
+    for (int r = 0; r <= P; ++r) c[r] = v[r];
+    return make_float4(c[0], c[1], c[2], c[3]);
 }
 
-// DER: cotangents of derivative channels present (H2, H3, K3 in use)
-template <int P, bool DER>
-__device__ void adj_block(const fa_block &B, const float *knots, int rx, int ry, int rz,
-                          uint32_t mask, int nch, const float *g, float *G, int b, int seg,
-                          int nseg, AdjSmem<DER> &sm) {
-    constexpr int kAdjWaves = adj_waves<DER>();
-    constexpr int kAdjRows = kAdjMaxYZ / kAdjWaves;  // y rows per wave
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    const int wave = tid >> 6, lane = tid & 63;
+// v[0..P] moved to ring order: plane s - P + r in slot (s - P + r) mod (P + 1)
+template <int P>
+__device__ __forceinline__ float4 ring4(const float (&v)[P + 1], int s) {
+    constexpr int R = P + 1;
+    const int base = (s - P) % R;
+    float c[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+        const int r = (m - base + R) % R;
+#pragma unroll
+        for (int q = 0; q < R; ++q) c[m] = r == q ? v[q] : c[m];
+    }
+    return make_float4(c[0], c[1], c[2], c[3]);
+}
+
+// RAG: the rows of the cotangent are not whole 16-byte vectors (the values a
+// load takes from past its row's end are replaced by zeros)
+template <int P, bool DER, bool RAG>
+__device__ __forceinline__ void adj_block(const fa_block &B, const float *knots, int rx, int ry,
+                                          int rz, uint32_t mask, const float *g, float *G, int b,
+                                          int seg, int nseg, AmSmem<DER> &sm) {
+    constexpr int R = P + 1;  // ring slots
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int gq = lane >> 4, l16 = lane & 15;
     const int nx = B.ncp[0], ny = B.ncp[1], nz = B.ncp[2];
-    const int nkn = nx + ny + nz + 3 * (P + 1);
-    for (int e = tid; e < nkn; e += nthr) sm.kn[e] = knots[B.knot_off + e];
-    for (int j = tid; j < FA_MAX_NCP; j += nthr) {
-        sm.jva[j] = sm.kwa[j] = 0x7fffffff;
-        sm.jvb[j] = sm.kwb[j] = -1;
+    const int i0 = seg * nx / nseg, i1 = (seg + 1) * nx / nseg;  // planes stored here
+    if (i0 >= i1) return;
+
+    // knots; span and basis tables of the y and z positions and the x slices
+    const int nkn = nx + ny + nz + 3 * R;
+    for (int e = tid; e < nkn; e += kAT) sm.kn[e] = knots[B.knot_off + e];
+    if (tid < kAM / 16) {
+        sm.tw[0][tid] = 0x7fffffff;
+        sm.tw[1][tid] = -1;
     }
     lds_barrier();
-    const float *tx = sm.kn, *ty = tx + nx + P + 1, *tz = ty + ny + P + 1;
-    for (int u = tid; u < rx; u += nthr) tab_axis<P>(tx, nx, rx, u, sm.xB[u], sm.xD[u], sm.xS[u]);
-    for (int v = tid; v < ry; v += nthr) {
-        tab_axis<P>(ty, ny, ry, v, sm.yB[v], sm.yD[v], sm.yS[v]);
-        for (int r = 0; r <= P; ++r) {
-            atomicMin(&sm.jva[sm.yS[v] - P + r], v);
-            atomicMax(&sm.jvb[sm.yS[v] - P + r], v);
+    const float *tx = sm.kn, *ty = tx + nx + R, *tz = ty + ny + R;
+    for (int t = tid; t < ry + rz; t += kAT) {
+        const bool isy = t < ry;
+        const int pos = isy ? t : t - ry;
+        const int n = isy ? ny : nz;
+        const float *tk = isy ? ty : tz;
+        const float x = grid_pos(pos, isy ? ry : rz);
+        const int s = span_search(n, P, tk, x);
+        float N[R], D[R];
+        basis_ders<P>(tk, s, x, N, D);
+        (isy ? sm.yN : sm.zN)[pos] = row4<P>(N);
+        if constexpr (DER) (isy ? sm.yD : sm.zD)[pos] = row4<P>(D);
+        (isy ? sm.ys : sm.zs)[pos] = s;
+        // the k tiles of 16 lattice indices this w position's window touches
+        if (!isy) {
+            for (int tt = (s - P) >> 4; tt <= s >> 4; ++tt) {
+                atomicMin(&sm.tw[0][tt], pos);
+                atomicMax(&sm.tw[1][tt], pos);
+            }
         }
     }
-    for (int w = tid; w < rz; w += nthr) {
-        tab_axis<P>(tz, nz, rz, w, sm.zB[w], sm.zD[w], sm.zS[w]);
-        for (int r = 0; r <= P; ++r) {
-            atomicMin(&sm.kwa[sm.zS[w] - P + r], w);
-            atomicMax(&sm.kwb[sm.zS[w] - P + r], w);
-        }
+    for (int u = tid; u < rx; u += kAT) {
+        const float x = grid_pos(u, rx);
+        const int s = span_search(nx, P, tx, x);
+        float N[R], D[R];
+        basis_ders<P>(tx, s, x, N, D);
+        sm.xB[u] = ring4<P>(N, s);
+        if constexpr (DER) sm.xD[u] = ring4<P>(D, s);
+        sm.xS[u] = s;
     }
     lds_barrier();
 
-    const int64_t vox = (int64_t)rx * ry * rz;
-    const int64_t plane = (int64_t)ry * rz;
-    const bool wok = lane < rz;
-    const int w = wok ? lane : 0;
-    const float *gb = g + (int64_t)b * nch * vox + w;
-    int64_t choff[4];
-    {
-        int c = 0;
-        for (int ch = 0; ch < 4; ++ch) {
-            choff[ch] = (int64_t)c * vox;
-            c += (mask >> ch) & 1u;
+    // entry (position pos, lattice index i) of the basis along z or y
+    auto zval = [&](int w, int k, const float4 *tab) {
+        if (w >= rz || k >= nz) return 0.0f;
+        const int d = k - (sm.zs[w] - P);
+        return d >= 0 && d <= P ? pick4(tab[w], d) : 0.0f;
+    };
+    auto yval = [&](int v, int j, const float4 *tab) {
+        if (v >= ry || j >= ny) return 0.0f;
+        const int d = j - (sm.ys[v] - P);
+        return d >= 0 && d <= P ? pick4(tab[v], d) : 0.0f;
+    };
+    if constexpr (DER) {
+        for (int e = tid; e < 4 * (kAM / 16) * 4 * kWave; e += kAT) {
+            const int l = e & (kWave - 1), q = (e >> 6) & 3, t = (e >> 8) & 3, d = (e >> 10) & 1;
+            const int p0 = 16 * q + 4 * (l >> 4), i = 16 * t + (l & 15);
+            float f[4];
+            if (e >> 11) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) f[r] = yval(p0 + r, i, d ? sm.yD : sm.yN);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) f[r] = zval(p0 + r, i, d ? sm.zD : sm.zN);
+            }
+            (e >> 11 ? sm.yop : sm.zop)[d][t][q][l] = make_float4(f[0], f[1], f[2], f[3]);
         }
+        lds_barrier();
     }
+
+    // waves: (chunk, j tile pair, k tile).  The segment's slices [slo, shi)
+    // are split into X chunks of consecutive slices; each chunk after the
+    // first starts at the first change of the span along x at or after slo +
+    // c (shi - slo) / X, when there is
+    // one (neighbouring chunks then share fewer control planes), and X is
+    // as large as the waves allow with every chunk non-empty and no control
+    // plane touched by three chunks.  (Values read from LDS that are the
+    // same in every lane go through readfirstlane, so the control flow they
+    // decide stays scalar.)
+    const int njt = (ny + 15) >> 4, nkt = (nz + 15) >> 4;
+    const int njp = (njt + 1) >> 1;
+    const int W1 = nkt * njp;
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    const int cw = wv / W1, wr = wv % W1;
+    uint64_t first[4];  // bit u % 64 of word u / 64: slice u starts a span
+    int slo = 0, shi = 0;  // spans are non-decreasing along x
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const int u = 64 * w + lane;
+        first[w] = __ballot(u < rx && u > 0 && sm.xS[u] != sm.xS[u - 1]);
+        slo += __builtin_popcountll(__ballot(u < rx && sm.xS[u] < i0));
+        shi += __builtin_popcountll(__ballot(u < rx && sm.xS[u] - P < i1));
+    }
+    const int plane = ny * nz;
     float *Gb = G + B.ctrl_off;
-
-    // sliding windows: planes top-P .. top, rows v = wave + 8 m
-    float hB[kAdjRows][P + 1], h2[DER ? kAdjRows : 1][P + 1], h3[DER ? kAdjRows : 1][P + 1];
+    if (slo >= shi) {  // no slice touches the segment's planes
+        for (int e = tid; e < (i1 - i0) * plane; e += kAT) Gb[(int64_t)i0 * plane + e] = 0.0f;
+        return;
+    }
+    auto next_start = [&](int u) -> int {  // the first span start >= u, else rx
 #pragma unroll
-    for (int m = 0; m < kAdjRows; ++m)
-#pragma unroll
-        for (int r = 0; r <= P; ++r) {
-            hB[m][r] = 0.0f;
-            if (DER) h2[m][r] = h3[m][r] = 0.0f;
+        for (int w = 0; w < 4; ++w) {
+            if (w < (u >> 6)) continue;
+            uint64_t m = first[w];
+            if (w == (u >> 6)) m &= ~0ull << (u & 63);
+            if (m) return min(64 * w + __builtin_ctzll(m), rx);
         }
-    int top = -1;
-
-    // write plane i (window slot 0) of every column, contract y then z, store
-    auto emit = [&](int i) {
-#pragma unroll
-        for (int m = 0; m < kAdjRows; ++m) {
-            const int v = wave + kAdjWaves * m;
-            if (v < ry) {
-                sm.H[0][v * kWave + lane] = wok ? hB[m][0] : 0.0f;
-                if (DER) {
-                    sm.H[1][v * kWave + lane] = wok ? h2[m][0] : 0.0f;
-                    sm.H[2][v * kWave + lane] = wok ? h3[m][0] : 0.0f;
-                }
-            }
-        }
-        lds_barrier();
-        for (int e = tid; e < ny * kWave; e += nthr) {
-            const int j = e >> 6, ww = e & 63;
-            float kb = 0.0f, k3 = 0.0f;
-            for (int v = sm.jva[j]; v <= sm.jvb[j]; ++v) {
-                const int r = j - (sm.yS[v] - P);
-                const float cb = comp4(sm.yB[v], r);
-                kb = fmaf(cb, sm.H[0][v * kWave + ww], kb);
-                if (DER) {
-                    kb = fmaf(comp4(sm.yD[v], r), sm.H[1][v * kWave + ww], kb);
-                    k3 = fmaf(cb, sm.H[2][v * kWave + ww], k3);
-                }
-            }
-            sm.K[0][e] = kb;
-            if (DER) sm.K[1][e] = k3;
-        }
-        lds_barrier();
-        for (int e = tid; e < ny * nz; e += nthr) {
-            const int j = e / nz, k = e - j * nz;
-            float acc = 0.0f;
-            for (int ww = sm.kwa[k]; ww <= sm.kwb[k]; ++ww) {
-                const int r = k - (sm.zS[ww] - P);
-                acc = fmaf(comp4(sm.zB[ww], r), sm.K[0][j * kWave + ww], acc);
-                if (DER) acc = fmaf(comp4(sm.zD[ww], r), sm.K[1][j * kWave + ww], acc);
-            }
-            Gb[((int64_t)i * ny + j) * nz + k] = acc;
-        }
-        lds_barrier();
+        return rx;
     };
-    // the control planes this segment owns
-    const int i0 = (int)((int64_t)seg * nx / nseg), i1 = (int)((int64_t)(seg + 1) * nx / nseg);
-    auto advance = [&]() {  // plane top-P is final; shift the windows by one
-        if (top - P >= i0 && top - P < i1) emit(top - P);
-#pragma unroll
-        for (int m = 0; m < kAdjRows; ++m) {
-#pragma unroll
-            for (int r = 0; r < P; ++r) {
-                hB[m][r] = hB[m][r + 1];
-                if (DER) {
-                    h2[m][r] = h2[m][r + 1];
-                    h3[m][r] = h3[m][r + 1];
-                }
-            }
-            hB[m][P] = 0.0f;
-            if (DER) h2[m][P] = h3[m][P] = 0.0f;
+    const int len = shi - slo;
+    int X = min(kAW / W1, len), ua = slo, ue = shi;  // this wave's chunk [ua, ue)
+    for (;; --X) {
+        bool ok = true;
+        int prev = slo;
+        ua = slo;
+        ue = shi;
+        for (int c = 1; c < X && ok; ++c) {
+            const int u0 = max(slo + c * len / X, prev + 1);
+            int u = next_start(u0);
+            if (u >= shi) u = u0;
+            ok = u < shi && (c < 2 || sm.xS[prev - 1] < sm.xS[u] - P);
+            if (c == cw) ua = u;
+            if (c == cw + 1) ue = u;
+            prev = u;
         }
-        ++top;
-    };
+        if (ok || X == 1) break;
+    }
+    // Small lattices, where X so chosen leaves two thirds of the waves idle: X
+    // as the waves allow with equal chunks, if every chunk's own copy of the
+    // planes it touches fits in LDS; each chunk leaves all of its planes there
+    // and the sums over the chunks follow the barrier (128 blocks of 8^3, all
+    // channels: 211 -> 151 us).  At half the waves idle the copies cost more
+    // than they give (128 blocks of 16..32, values: 51 us without, 59 with).
+    const int XO = min(kAW / W1, len);
+    int lbase = 0;
+    bool open = false;
+    if (3 * X <= XO) {
+        int total = 0;
+        for (int c = 0; c < XO; ++c) {
+            if (c == cw) lbase = total;
+            total += (sm.xS[slo + (c + 1) * len / XO - 1] - sm.xS[slo + c * len / XO] + R) * plane;
+        }
+        open = __builtin_amdgcn_readfirstlane(total) <= kLB;
+        lbase = __builtin_amdgcn_readfirstlane(lbase);
+        if (open) {
+            X = XO;
+            ua = slo + cw * len / XO;
+            ue = slo + (cw + 1) * len / XO;
+        }
+    }
+    X = __builtin_amdgcn_readfirstlane(X);
+    ua = __builtin_amdgcn_readfirstlane(ua);
+    ue = __builtin_amdgcn_readfirstlane(ue);
+    const int c = cw;
+    const bool active = c < X;
+    const int nt = wr % nkt, jp = wr / nkt;
+    const int ub = ue - 1;
+    const int Lc = __builtin_amdgcn_readfirstlane(sm.xS[active ? ua : slo] - P);
+    // last plane of chunk c-1, first plane of chunk c+1
+    const int Hprev = c > 0 && active ? __builtin_amdgcn_readfirstlane(sm.xS[ua - 1]) : -1;
+    const int Lnext = c + 1 < X ? __builtin_amdgcn_readfirstlane(sm.xS[ue] - P) : nx;
+    const int k = 16 * nt + l16;
 
-    // cotangent rows of x position u, loaded one step ahead of their use
-    float g0[kAdjRows], g1[kAdjRows], g2[kAdjRows], g3[kAdjRows];
-    float n0[kAdjRows], n1[kAdjRows], n2[kAdjRows], n3[kAdjRows];
-    auto fetch = [&](int u, float(&f0)[kAdjRows], float(&f1)[kAdjRows], float(&f2)[kAdjRows],
-                     float(&f3)[kAdjRows]) {
-        const float *gu = gb + (int64_t)u * plane;
+    f32x4a ring[kJT][R];
 #pragma unroll
-        for (int m = 0; m < kAdjRows; ++m) {
-            const int v = wave + kAdjWaves * m;
-            const bool ok = u < rx && wok && v < ry;
-            const float *gp = gu + (int64_t)(ok ? v : 0) * rz;
-            f0[m] = (ok && (mask & 1u)) ? gp[choff[0]] : 0.0f;
-            f1[m] = (ok && DER && (mask & 2u)) ? gp[choff[1]] : 0.0f;
-            f2[m] = (ok && DER && (mask & 4u)) ? gp[choff[2]] : 0.0f;
-            f3[m] = (ok && DER && (mask & 8u)) ? gp[choff[3]] : 0.0f;
-        }
-    };
-    // x positions whose basis touches [i0, i1): spans s(u) in [i0, i1 - 1 + P]
-    // (s(u) is non-decreasing in u)
-    int ulo = 0, uhi = rx - 1;
-    while (ulo < rx && sm.xS[ulo] < i0) ++ulo;
-    while (uhi >= ulo && sm.xS[uhi] - P > i1 - 1) --uhi;
-    if (i0 < i1) {
-        fetch(ulo, g0, g1, g2, g3);
-        for (int u = ulo; u <= uhi; ++u) {
-            if (u + 1 <= uhi) fetch(u + 1, n0, n1, n2, n3);
-            const int s = sm.xS[u];
-            while (top < s) advance();  // uniform over the workgroup
-            const float4 bx = sm.xB[u], dx = sm.xD[u];
+    for (int jj = 0; jj < kJT; ++jj)
 #pragma unroll
-            for (int m = 0; m < kAdjRows; ++m) {
+        for (int m = 0; m < R; ++m) ring[jj][m] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
+    // plane i of the wave's tiles: into G, or (dst != null) into a partial
+    // plane buffer; with add, the buffer's values are added first.  Element
+    // (j, k) of a plane is lane_e + (16 jt + r) nz; G is written through a
+    // buffer resource, the plane and row in the scalar offset.
+    const __amdgpu_buffer_rsrc_t gs = make_rsrc(Gb, (uint32_t)((int64_t)nx * plane * 4));
+    const int lane_e = 4 * gq * nz + k;
+    const int lplane = open ? lbase : (c - 1) * R * plane;  // this chunk's planes in LDS
+    auto put_plane = [&](int slot, float *dst, int i, const float *add)
+        __attribute__((always_inline)) {
+        const bool mine = i >= i0 && i < i1;
+        // opaque, so that the masks below are formed here and not kept in
+        // scalar registers through the slice loop
+        int j0 = 4 * gq, kk = k;
+        asm volatile("" : "+v"(j0), "+v"(kk));
 #pragma unroll
-                for (int r = 0; r <= P; ++r) {
-                    hB[m][r] = fmaf(comp4(bx, r), g0[m], hB[m][r]);
-                    if (DER) {
-                        hB[m][r] = fmaf(comp4(dx, r), g1[m], hB[m][r]);
-                        h2[m][r] = fmaf(comp4(bx, r), g2[m], h2[m][r]);
-                        h3[m][r] = fmaf(comp4(bx, r), g3[m], h3[m][r]);
+        for (int jj = 0; jj < kJT; ++jj) {
+            const int jt = 2 * jp + jj;
+            if (jt >= njt) continue;
+#pragma unroll
+            for (int m = 0; m < R; ++m) {
+                if (m != slot) continue;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = (16 * jt + r) * nz;  // uniform
+                    if ((dst || mine) && 16 * jt + j0 + r < ny && kk < nz) {
+                        float v = ring[jj][m][r];
+                        if (add) v = add[lane_e + row] + v;
+                        if (dst) dst[lane_e + row] = v;
+                        else
+                            __builtin_amdgcn_raw_buffer_store_b32(
+                                __float_as_uint(v), gs, (uint32_t)lane_e * 4u,
+                                (uint32_t)(i * plane + row) * 4u, 0);
                     }
                 }
-            }
-#pragma unroll
-            for (int m = 0; m < kAdjRows; ++m) {
-                g0[m] = n0[m];
-                g1[m] = n1[m];
-                g2[m] = n2[m];
-                g3[m] = n3[m];
+                ring[jj][m] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
             }
         }
-        // the owned planes not emitted yet (also those no x position touches)
-        while (top - P < i1) advance();
+    };
+    // a completed plane of this chunk: shared with the chunk to the left
+    // (its partial goes to LDS) or this chunk's alone (stored)
+    auto flush = [&](int i) __attribute__((always_inline)) {
+        if (open || i <= Hprev)
+            put_plane(i % R, sm.lb + lplane + (i - Lc) * plane, i, nullptr);
+        else
+            put_plane(i % R, nullptr, i, nullptr);
+    };
+
+    int top = Lc - 1;  // newest plane in the ring
+    if (active) {
+        // the k tile's z band: the 16-column groups q = q0 + q', q' < nq, in
+        // which some w has a basis entry for one of the tile's k (a tile no
+        // position touches takes one group of zero weights)
+        const int qlo = __builtin_amdgcn_readfirstlane(sm.tw[0][nt] >> 4);
+        const int qhi = __builtin_amdgcn_readfirstlane(sm.tw[1][nt] >> 4);
+        const int nq = qhi >= qlo ? qhi - qlo + 1 : 1;
+        const int q0 = qhi >= qlo ? qlo : 0;
+        // values only: operands held for the whole block, the z basis at the
+        // lane's w = 16 (q0 + q') + 4 gq + j for its k, the y basis at its 16
+        // v positions for its j (zero outside each j tile's band, so the y
+        // product runs over all four row bands)
+        float bzs[4][4], by[4][4][kJT];
+        if constexpr (!DER) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    bzs[q][j] = zval(16 * (q0 + q) + 4 * gq + j, k, sm.zN);
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int jj = 0; jj < kJT; ++jj)
+                        by[mt][r][jj] = yval(16 * mt + 4 * gq + r, 16 * (2 * jp + jj) + l16, sm.yN);
+        }
+
+        // slice loads: 16 bytes of row 16 m + l16 at w = 16 q + 4 gq, rows
+        // and columns clamped into the slice (the bases are zero there, so
+        // the values read have no weight; every lane issues the same loads):
+        // a buffer resource over the block, the lane's row and column in
+        // one 32-bit offset, the channel and slice in the scalar offset.  In
+        // rows that are not whole vectors the last load of a row runs past
+        // its end (past the block's end it reads zeros), and the values of
+        // no column are zeroed before use.
+        const int64_t vox = (int64_t)rx * ry * rz;
+        const int nch = __builtin_popcount(mask);
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(g + (int64_t)b * nch * vox,
+                                                    (uint32_t)(nch * vox * 4));
+        uint32_t roff[4], coff[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            roff[t] = (uint32_t)(min(16 * t + l16, ry - 1) * rz * 4);
+            coff[t] = (uint32_t)(min(16 * t + 4 * gq, (rz - 1) & ~3) * 4);
+        }
+        const uint32_t sbytes = (uint32_t)(ry * rz * 4);
+        auto load = [&](uint32_t at, int mt, int q) -> float4 {
+            const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, roff[mt] + coff[q], at, 0);
+            return make_float4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]),
+                               __uint_as_float(x[3]));
+        };
+        const int nj = min(2, njt - 2 * jp);
+        // the slice loop, straight-line code for each (nq, one or two j tiles)
+        auto slices = [&](auto NQc, auto NJc) __attribute__((always_inline)) {
+            constexpr int NQ = decltype(NQc)::value, NJ = decltype(NJc)::value;
+            auto loads = [&](uint32_t at, float4(&f)[4][NQ]) {
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) f[mt][q] = load(at, mt, min(q0 + q, 3));
+            };
+            // value j of a load of column group q, zero past the row's end
+            auto val = [&](const float4 &f, int q, int j) {
+                const float x = j == 0 ? f.x : (j == 1 ? f.y : (j == 2 ? f.z : f.w));
+                return RAG && 16 * min(q0 + q, 3) + 4 * gq + j >= rz ? 0.0f : x;
+            };
+            // advance the ring to slice u's span
+            auto advance = [&](int u) __attribute__((always_inline)) {
+                const int s = __builtin_amdgcn_readfirstlane(sm.xS[u]);
+                while (top < s) {  // uniform: plane top+1 enters, plane top-P leaves
+                    ++top;
+                    if (top - R >= Lc) flush(top - R);
+                }
+            };
+          if constexpr (!DER) {
+            float4 ga[4][NQ];
+            loads((uint32_t)ua * sbytes, ga);
+            for (int u = ua; u <= ub; ++u) {
+                const int un = u < ub ? u + 1 : u;  // the next slice (the last one again at the end)
+                // z: four independent chains (one per 16-row band)
+                f32x4a Z[4];
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt) Z[mt] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int mt = 0; mt < 4; ++mt)
+                            Z[mt] = mma4(val(ga[mt][q], q, j), bzs[q][j], Z[mt]);
+                // the next slice, in flight during the rest of this one
+                loads((uint32_t)un * sbytes, ga);
+                // y: the y basis is zero outside each j tile's band
+                f32x4a Y[kJT], Yo[kJT];
+#pragma unroll
+                for (int jj = 0; jj < kJT; ++jj) Y[jj] = Yo[jj] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                    for (int jj = 0; jj < NJ; ++jj) {
+                        Y[jj] = mma4(by[mt][0][jj], Z[mt][0], Y[jj]);
+                        Yo[jj] = mma4(by[mt][1][jj], Z[mt][1], Yo[jj]);
+                        Y[jj] = mma4(by[mt][2][jj], Z[mt][2], Y[jj]);
+                        Yo[jj] = mma4(by[mt][3][jj], Z[mt][3], Yo[jj]);
+                    }
+#pragma unroll
+                for (int jj = 0; jj < NJ; ++jj) Y[jj] += Yo[jj];
+                // x contraction: advance the ring to this slice's span, then
+                // add its contributions to the p+1 planes it touches
+                advance(u);
+                const float4 cx = sm.xB[u];
+                const float cf[4] = {cx.x, cx.y, cx.z, cx.w};
+#pragma unroll
+                for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+                    for (int m = 0; m < R; ++m)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            ring[jj][m][r] = fmaf(cf[m], Y[jj][r], ring[jj][m][r]);
+            }
+          } else {
+            // channels 1, 0, 3, 2 of a slice in turn, two buffers, each
+            // reloaded two channels ahead once its z product has read it; one
+            // Z tile set is live at a time
+            const uint32_t vb = (uint32_t)(vox * 4);
+            // a channel that is not there reads zeros past the resource's end
+            auto at = [&](int u, int ch) {
+                return mask & (1u << ch)
+                           ? (uint32_t)__builtin_popcount(mask & ((1u << ch) - 1u)) * vb +
+                                 (uint32_t)u * sbytes
+                           : 0x40000000u;
+            };
+            float4 ga[4][NQ], gb[4][NQ];
+            loads(at(ua, 1), ga);
+            loads(at(ua, 0), gb);
+            for (int u = ua; u <= ub; ++u) {
+                const int un = u < ub ? u + 1 : u;
+                int ln = lane;  // opaque: the operands stay in LDS
+                asm volatile("" : "+v"(ln));
+                f32x4a Z[4];
+                auto zero = [&](f32x4a *f, int n) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int m = 0; m < n; ++m) f[m] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
+                };
+                auto zmul = [&](const float4(&f)[4][NQ], int d) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) {
+                        const float4 o = sm.zop[d][nt][min(q0 + q, 3)][ln];
+                        const float ov[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+#pragma unroll
+                            for (int mt = 0; mt < 4; ++mt)
+                                Z[mt] = mma4(val(f[mt][q], q, j), ov[j], Z[mt]);
+                    }
+                };
+                // two chains per j tile (even and odd K steps)
+                f32x4a Yb[kJT], Yo[kJT], Yd[kJT];
+                auto ymul = [&](int d, f32x4a(&Y)[kJT]) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                        for (int jj = 0; jj < NJ; ++jj) {
+                            const float4 o = sm.yop[d][2 * jp + jj][mt][ln];
+                            Y[jj] = mma4(o.x, Z[mt][0], Y[jj]);
+                            Yo[jj] = mma4(o.y, Z[mt][1], Yo[jj]);
+                            Y[jj] = mma4(o.z, Z[mt][2], Y[jj]);
+                            Yo[jj] = mma4(o.w, Z[mt][3], Yo[jj]);
+                        }
+                };
+                zero(Yd, kJT);
+                zero(Yo, kJT);
+                zero(Z, 4);
+                if (mask & 2u) zmul(ga, 0);
+                loads(at(u, 3), ga);
+                if (mask & 2u) ymul(0, Yd);
+#pragma unroll
+                for (int jj = 0; jj < NJ; ++jj) Yd[jj] += Yo[jj];
+                zero(Yb, kJT);
+                zero(Yo, kJT);
+                zero(Z, 4);
+                if (mask & 1u) zmul(gb, 0);
+                loads(at(u, 2), gb);
+                if (mask & 8u) zmul(ga, 1);
+                loads(at(un, 1), ga);
+                if (mask & 9u) ymul(0, Yb);
+                zero(Z, 4);
+                if (mask & 4u) zmul(gb, 0);
+                loads(at(un, 0), gb);
+                if (mask & 4u) ymul(1, Yb);
+#pragma unroll
+                for (int jj = 0; jj < NJ; ++jj) Yb[jj] += Yo[jj];
+                advance(u);
+                const float4 cx = sm.xB[u], ex = sm.xD[u];
+                const float cf[4] = {cx.x, cx.y, cx.z, cx.w}, ef[4] = {ex.x, ex.y, ex.z, ex.w};
+#pragma unroll
+                for (int jj = 0; jj < NJ; ++jj)
+#pragma unroll
+                    for (int m = 0; m < R; ++m)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            ring[jj][m][r] = fmaf(cf[m], Yb[jj][r],
+                                                  fmaf(ef[m], Yd[jj][r], ring[jj][m][r]));
+            }
+          }
+        };
+        using I1 = std::integral_constant<int, 1>;
+        using I2 = std::integral_constant<int, 2>;
+        using I3 = std::integral_constant<int, 3>;
+        using I4 = std::integral_constant<int, 4>;
+        if (nj == 2) {
+            if (nq == 4) slices(I4{}, I2{});
+            else if (nq == 3) slices(I3{}, I2{});
+            else if (nq == 2) slices(I2{}, I2{});
+            else slices(I1{}, I2{});
+        } else {
+            if (nq == 4) slices(I4{}, I1{});
+            else if (nq == 3) slices(I3{}, I1{});
+            else if (nq == 2) slices(I2{}, I1{});
+            else slices(I1{}, I1{});
+        }
+        // planes between this chunk's last and the next chunk's first (no
+        // slice touches them when the x span jumps by more than p+1 between
+        // neighbouring slices) leave the ring as zeros
+        while (!open && c + 1 < X && top < Lnext - 1) {
+            ++top;
+            if (top - R >= Lc) flush(top - R);
+        }
+        // planes still in the ring that no chunk to the right shares
+        for (int i = max(Lc, top - P); i <= top && (open || i < Lnext); ++i) flush(i);
     }
+    lds_barrier();  // left partial planes of every chunk in LDS
+    if (open) {
+        // every plane of the segment: the chunks that touch it, in order
+        for (int e = tid; e < (i1 - i0) * plane; e += kAT) {
+            const int i = i0 + e / plane, r = e - (i - i0) * plane;
+            float sum = 0.0f;
+            int at = 0;
+            for (int c = 0; c < X; ++c) {
+                const int lo = sm.xS[slo + c * len / X] - P;
+                const int hi = sm.xS[slo + (c + 1) * len / X - 1];
+                if (i >= lo && i <= hi) sum += sm.lb[at + (i - lo) * plane + r];
+                at += (hi - lo + 1) * plane;
+            }
+            Gb[(int64_t)i * plane + r] = sum;
+        }
+        return;
+    }
+    if (active && c + 1 < X) {
+        // planes shared with the chunk to the right: its partial + this one
+        for (int i = Lnext; i <= top; ++i)
+            put_plane(i % R, nullptr, i, sm.lb + (c * R + (i - Lnext)) * plane);
+    }
+    // planes of the segment that no slice touches, before its first slice's
+    // and after its last one's
+    const int lo = __builtin_amdgcn_readfirstlane(sm.xS[slo]) - P;
+    const int hl = max(__builtin_amdgcn_readfirstlane(sm.xS[shi - 1]) + 1, i0);
+    for (int e = tid; e < (min(lo, i1) - i0) * plane; e += kAT) Gb[(int64_t)i0 * plane + e] = 0.0f;
+    for (int e = tid; e < (i1 - hl) * plane; e += kAT) Gb[(int64_t)hl * plane + e] = 0.0f;
 }
 
-template <bool DER>
-__global__ __launch_bounds__(64 * adj_waves<DER>()) void adjoint_kernel(
-    const fa_block *blocks, int nblocks, int nseg, const float *knots, int rx, int ry, int rz,
-    uint32_t mask, int nch, const float *g, float *G) {
+template <bool DER, bool RAG>
+__global__ __launch_bounds__(kAT) void adjoint_kernel(const fa_block *blocks, int nseg,
+                                                      const float *knots, int rx, int ry, int rz,
+                                                      uint32_t mask, const float *g, float *G) {
     extern __shared__ float4 dyn_lds[];
-    AdjSmem<DER> &sm = *reinterpret_cast<AdjSmem<DER> *>(dyn_lds);
-    const int64_t items = (int64_t)nblocks * nseg;
-    for (int64_t it = xcd_order(blockIdx.x, gridDim.x); it < items; it += gridDim.x) {
-        const int b = (int)(it / nseg), seg = (int)(it - (int64_t)b * nseg);
-        const fa_block &B = blocks[b];
-        const int p = B.degree[0];
-        if (p == 3) adj_block<3, DER>(B, knots, rx, ry, rz, mask, nch, g, G, b, seg, nseg, sm);
-        else if (p == 2) adj_block<2, DER>(B, knots, rx, ry, rz, mask, nch, g, G, b, seg, nseg, sm);
-        else adj_block<1, DER>(B, knots, rx, ry, rz, mask, nch, g, G, b, seg, nseg, sm);
-        lds_barrier();
-    }
+    AmSmem<DER> &sm = *reinterpret_cast<AmSmem<DER> *>(dyn_lds);
+    // one workgroup per (micro-model, segment)
+    const int b = blockIdx.x / nseg, seg = blockIdx.x - b * nseg;
+    const fa_block &B = blocks[b];
+    const int p = B.degree[0];
+    if (p == 3) adj_block<3, DER, RAG>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
+    else if (p == 2) adj_block<2, DER, RAG>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
+    else adj_block<1, DER, RAG>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
+}
+
+template <bool DER, bool RAG>
+hipError_t launch(const fa_block *blocks, int nblocks, const float *knots, int rx, int ry, int rz,
+                  uint32_t mask, const float *g, float *G, hipStream_t s) {
+    // raise the dynamic LDS limit once per process (before any graph capture)
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void *>(&adjoint_kernel<DER, RAG>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(AmSmem<DER>));
+    if (attr != hipSuccess) return attr;
+    // one workgroup fits a CU: segments while a CU would be without one
+    const int nseg = std::max(1, std::min(kMaxSegs, kCUs / nblocks));
+    hipLaunchKernelGGL((adjoint_kernel<DER, RAG>), dim3((unsigned)nblocks * nseg), dim3(kAT),
+                       sizeof(AmSmem<DER>), s, blocks, nseg, knots, rx, ry, rz, mask, g, G);
+    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_adjoint(const fa_block *blocks, int nblocks, const float *knots, int rx,
-                          int ry, int rz, uint32_t mask, const float *g, float *G, int /*it*/,
-                          hipStream_t s) {
-    if ((mask & 15u) == 1u) {  // the value channel alone: the matrix-core form
-        const hipError_t e = launch_adjoint_value(blocks, nblocks, knots, rx, ry, rz, g, G, s);
-        if (e != hipErrorNotSupported) return e;  // else rows it cannot load as 16-byte vectors
-    }
-    const int nch = __builtin_popcount(mask & 15u);  // derivative channels present
-    // raise the dynamic LDS limit once per process (before any graph capture)
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&adjoint_kernel<true>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(AdjSmem<true>));
-    if (attr != hipSuccess) return attr;
-    const int grid = nblocks < 65536 ? nblocks : 65536;
-    hipLaunchKernelGGL((adjoint_kernel<true>), dim3(grid), dim3(64 * adj_waves<true>()),
-                       sizeof(AdjSmem<true>), s, blocks, nblocks, 1, knots, rx, ry, rz, mask, nch,
-                       g, G);
-    return hipGetLastError();
+hipError_t launch_adjoint(const fa_block *blocks, int nblocks, const float *knots, int rx, int ry,
+                          int rz, uint32_t mask, const float *g, float *G, hipStream_t s) {
+    if (ry > kAM || rz > kAM) return hipErrorNotSupported;
+    if (nblocks <= 0) return hipSuccess;
+    mask &= 15u;
+    const bool rag = (rz & 3) != 0;
+    if (mask == 1u)
+        return rag ? launch<false, true>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s)
+                   : launch<false, false>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s);
+    return rag ? launch<true, true>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s)
+               : launch<true, false>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s);
 }
 
 }  // namespace fa

@@ -509,7 +509,7 @@ fa_status fa_decode_backward(const fa_block *blocks, int32_t nblocks, const floa
         return FA_ERR_INVALID_ARG;
     if (!res_supported(res) || res[1] > 64 || res[2] > 64) return FA_ERR_UNSUPPORTED;
     hipError_t e = launch_adjoint(blocks, nblocks, knots, res[0], res[1], res[2], mask,
-                                  grad_out, grad_ctrl, 0, (hipStream_t)stream);
+                                  grad_out, grad_ctrl, (hipStream_t)stream);
     return e == hipSuccess ? FA_OK : FA_ERR_DEVICE;
 }
 
@@ -659,9 +659,15 @@ bool search_supported(const int32_t res[3], int32_t degree, int32_t ncp_hi) {
 int64_t fa_ncp_search_workspace(int32_t nblocks, const int32_t res[3], int32_t degree,
                                 int32_t ncp_hi) {
     if (nblocks <= 0 || !res_ok(res) || degree < 1 || ncp_hi < degree + 1) return -1;
-    return std::max(search_least(nblocks, res, degree, ncp_hi),
-                    search_layout(nblocks, res, degree, ncp_hi,
-                                  search_group(nblocks, degree, ncp_hi), true).total);
+    return search_least(nblocks, res, degree, ncp_hi);
+}
+
+int64_t fa_ncp_search_workspace_wide(int32_t nblocks, const int32_t res[3], int32_t degree,
+                                     int32_t ncp_hi) {
+    const int64_t least = fa_ncp_search_workspace(nblocks, res, degree, ncp_hi);
+    if (least < 0) return -1;
+    return std::max(least, search_layout(nblocks, res, degree, ncp_hi,
+                                         search_group(nblocks, degree, ncp_hi), true).total);
 }
 
 fa_status fa_ncp_search(const float *samples, int32_t nblocks, const int32_t res[3],

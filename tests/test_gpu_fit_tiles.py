@@ -52,23 +52,12 @@ def test_search_with_the_least_workspace():
     lo, hi = 4, 16
     ref = fa.ncp_search(y, p, lo, hi)
     res = (ctypes.c_int32 * 3)(*R)
-    need = fa.lib.fa_ncp_search_workspace(nb, res, p, hi)
-    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
-    out = torch.empty_like(ref)
-
-    def call(size):
-        return fa.lib.fa_ncp_search(y.data_ptr(), nb, res, p, lo, hi, out.data_ptr(), ws.data_ptr(),
-                                    size, torch.cuda.current_stream().cuda_stream)
-
-    bad, ok = 0, need
-    while ok - bad > 1:
-        mid = (bad + ok) // 2
-        out.fill_(-1.0)
-        if call(mid) == fa.FA_OK:
-            ok = mid
-            assert torch.equal(out, ref)
-        else:
-            bad = mid
-            assert (out == -1.0).all()
-    assert ok < need
-    assert call(need) == fa.FA_OK and torch.equal(out, ref)
+    least = fa.lib.fa_ncp_search_workspace(nb, res, p, hi)
+    wide = fa.lib.fa_ncp_search_workspace_wide(nb, res, p, hi)
+    assert wide > least
+    ws = torch.empty(wide, dtype=torch.uint8, device="cuda")
+    for size in (least, wide - 1, wide):
+        out = torch.full_like(ref, -1.0)
+        assert fa.lib.fa_ncp_search(y.data_ptr(), nb, res, p, lo, hi, out.data_ptr(), ws.data_ptr(), size,
+                                    torch.cuda.current_stream().cuda_stream) == fa.FA_OK
+        assert torch.equal(out, ref), size
