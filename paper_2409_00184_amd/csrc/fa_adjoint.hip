@@ -406,8 +406,12 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
             coff[t] = (uint32_t)(min(16 * t + 4 * gq, (rz - 1) & ~3) * 4);
         }
         const uint32_t sbytes = (uint32_t)(ry * rz * 4);
-        auto load = [&](uint32_t at, int mt, int q) -> float4 {
-            const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(rs, roff[mt] + coff[q], at, 0);
+        // (the range check need not see the scalar offset: where a load may
+        // leave the block, all of its offset is in the vector part)
+        auto load = [&](uint32_t at, uint32_t dead, int mt, int q) -> float4 {
+            const uint32_t in = roff[mt] + coff[q];
+            const u32x4 x = RAG || DER ? __builtin_amdgcn_raw_buffer_load_b128(rs, in + (at + dead), 0, 0)
+                                : __builtin_amdgcn_raw_buffer_load_b128(rs, in + dead, at, 0);
             return make_float4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]),
                                __uint_as_float(x[3]));
         };
@@ -415,11 +419,11 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         // the slice loop, straight-line code for each (nq, one or two j tiles)
         auto slices = [&](auto NQc, auto NJc) __attribute__((always_inline)) {
             constexpr int NQ = decltype(NQc)::value, NJ = decltype(NJc)::value;
-            auto loads = [&](uint32_t at, float4(&f)[4][NQ]) {
+            auto loads = [&](uint32_t at, uint32_t dead, float4(&f)[4][NQ]) {
 #pragma unroll
                 for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-                    for (int q = 0; q < NQ; ++q) f[mt][q] = load(at, mt, min(q0 + q, 3));
+                    for (int q = 0; q < NQ; ++q) f[mt][q] = load(at, dead, mt, min(q0 + q, 3));
             };
             // value j of a load of column group q, zero past the row's end
             auto val = [&](const float4 &f, int q, int j) {
@@ -436,7 +440,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
             };
           if constexpr (!DER) {
             float4 ga[4][NQ];
-            loads((uint32_t)ua * sbytes, ga);
+            loads((uint32_t)ua * sbytes, 0u, ga);
             for (int u = ua; u <= ub; ++u) {
                 const int un = u < ub ? u + 1 : u;  // the next slice (the last one again at the end)
                 // z: four independent chains (one per 16-row band)
@@ -451,7 +455,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                         for (int mt = 0; mt < 4; ++mt)
                             Z[mt] = mma4(val(ga[mt][q], q, j), bzs[q][j], Z[mt]);
                 // the next slice, in flight during the rest of this one
-                loads((uint32_t)un * sbytes, ga);
+                loads((uint32_t)un * sbytes, 0u, ga);
                 // y: the y basis is zero outside each j tile's band
                 f32x4a Y[kJT], Yo[kJT];
 #pragma unroll
@@ -486,15 +490,14 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
             // Z tile set is live at a time
             const uint32_t vb = (uint32_t)(vox * 4);
             // a channel that is not there reads zeros past the resource's end
-            auto at = [&](int u, int ch) {
-                return mask & (1u << ch)
-                           ? (uint32_t)__builtin_popcount(mask & ((1u << ch) - 1u)) * vb +
-                                 (uint32_t)u * sbytes
-                           : 0x40000000u;
+            auto fetch = [&](int u, int ch, float4(&f)[4][NQ]) __attribute__((always_inline)) {
+                const bool has = mask & (1u << ch);
+                const uint32_t c = (uint32_t)__builtin_popcount(mask & ((1u << ch) - 1u));
+                loads(has ? c * vb + (uint32_t)u * sbytes : 0u, has ? 0u : 0x40000000u, f);
             };
             float4 ga[4][NQ], gb[4][NQ];
-            loads(at(ua, 1), ga);
-            loads(at(ua, 0), gb);
+            fetch(ua, 1, ga);
+            fetch(ua, 0, gb);
             for (int u = ua; u <= ub; ++u) {
                 const int un = u < ub ? u + 1 : u;
                 int ln = lane;  // opaque: the operands stay in LDS
@@ -534,7 +537,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                 zero(Yo, kJT);
                 zero(Z, 4);
                 if (mask & 2u) zmul(ga, 0);
-                loads(at(u, 3), ga);
+                fetch(u, 3, ga);
                 if (mask & 2u) ymul(0, Yd);
 #pragma unroll
                 for (int jj = 0; jj < NJ; ++jj) Yd[jj] += Yo[jj];
@@ -542,13 +545,13 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                 zero(Yo, kJT);
                 zero(Z, 4);
                 if (mask & 1u) zmul(gb, 0);
-                loads(at(u, 2), gb);
+                fetch(u, 2, gb);
                 if (mask & 8u) zmul(ga, 1);
-                loads(at(un, 1), ga);
+                fetch(un, 1, ga);
                 if (mask & 9u) ymul(0, Yb);
                 zero(Z, 4);
                 if (mask & 4u) zmul(gb, 0);
-                loads(at(un, 0), gb);
+                fetch(un, 0, gb);
                 if (mask & 4u) ymul(1, Yb);
 #pragma unroll
                 for (int jj = 0; jj < NJ; ++jj) Yb[jj] += Yo[jj];

@@ -314,8 +314,9 @@ __device__ __forceinline__ void fit_zy_block(const FitArgs &a, int bi, int x0, i
     const int gq = lane >> 4, l16 = lane & 15;
     const int r1 = a.r1, r2 = a.r2;
     const uint32_t slice = (uint32_t)r1 * (uint32_t)r2 * 4u;
-    // rows and columns outside the slice load at an offset beyond the
-    // resource and read as zero
+    // rows and columns outside the slice load at a vector offset beyond the
+    // resource and read as zero (the range check need not see the scalar
+    // offset, so nothing relies on that one leaving the resource)
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(
         a.y + (int64_t)(bi % a.nsrc) * a.r0 * r1 * r2, (uint32_t)a.r0 * slice);
     uint32_t row[4], col[4];
@@ -330,7 +331,7 @@ __device__ __forceinline__ void fit_zy_block(const FitArgs &a, int bi, int x0, i
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                s[t][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, row[t] + col[q], at, 0);
+                s[t][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, row[t] + col[q] + at, 0, 0);
             }
     };
     auto trim = [&](u32x4(&s)[4][4]) {  // the part of the last load past its row's end
@@ -350,8 +351,9 @@ __device__ __forceinline__ void fit_zy_block(const FitArgs &a, int bi, int x0, i
     int x = x0 + wave;
     if (x < x1) load((uint32_t)x * slice, cur);
     for (; x < x1; x += kZyWaves) {
-        // the next slice, in flight during all of this one
-        load(x + kZyWaves < x1 ? (uint32_t)(x + kZyWaves) * slice : kDeadFit, nxt);
+        // the next slice (at the end the last one again), in flight during all
+        // of this one
+        load((uint32_t)(x + kZyWaves < x1 ? x + kZyWaves : x) * slice, nxt);
         trim(cur);
         fit_zy_slice<NT, NJ>(oz, oy, cur, nq, nk, ny, nz, lane, U, (uint32_t)x * ub);
 #pragma unroll
@@ -408,8 +410,8 @@ __device__ __forceinline__ void fit_x_tiles(const FitArgs &a, int t0, int t1, in
                                             const double *U, const double *ox, float *P) {
     const int wave = uni32(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int gq = lane >> 4, l16 = lane & 15;
-    // rows x >= r0 and i >= n_x lie past the resources' ends, tiles past the
-    // last at a dead offset: the loop issues the same accesses every time
+    // rows x >= r0 and i >= n_x and tiles past the last are at a dead vector
+    // offset: the loop issues the same accesses every time
     const uint32_t ub = (uint32_t)ne * 8u, pb = (uint32_t)ne * 4u;
     const __amdgpu_buffer_rsrc_t ur = make_rsrc(U, (uint32_t)a.r0 * ub);
     const __amdgpu_buffer_rsrc_t pr = make_rsrc(P, (uint32_t)nx * pb);
@@ -418,8 +420,9 @@ __device__ __forceinline__ void fit_x_tiles(const FitArgs &a, int t0, int t1, in
         const uint32_t at = t < t1 && e < ne ? (uint32_t)gq * ub + (uint32_t)e * 8u : kDeadFit;
 #pragma unroll
         for (int ks = 0; ks < kOpSteps; ++ks)
-            u[ks] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
-                                                   ur, at, (uint32_t)(4 * ks) * ub, 0));
+            u[ks] = __builtin_bit_cast(
+                double, __builtin_amdgcn_raw_buffer_load_b64(ur, 4 * ks + gq < a.r0 ? at : kDeadFit,
+                                                             (uint32_t)(4 * ks) * ub, 0));
     };
     double cur[kOpSteps], nxt[kOpSteps];
     int t = t0 + wave;
@@ -442,7 +445,8 @@ __device__ __forceinline__ void fit_x_tiles(const FitArgs &a, int t0, int t1, in
         for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)acc[i][r]), pr, at,
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)acc[i][r]), pr,
+                                                      16 * i + 4 * r + gq < nx ? at : kDeadFit,
                                                       (uint32_t)(16 * i + 4 * r) * pb, 0);
 #pragma unroll
         for (int ks = 0; ks < kOpSteps; ++ks) cur[ks] = nxt[ks];
