@@ -104,17 +104,22 @@ typedef struct fa_work {
 /* Tunables of the batched decode (a0: batch plan and persistent schedule).
  * Zero fields take defaults. */
 typedef struct fa_tune {
-    int32_t rows_per_item; /* y rows per work item, 1..64 (default 8)           */
-    int32_t waves;         /* waves (64 lanes) per workgroup: 1, 2, 4, 8        */
-    int32_t grid;          /* persistent workgroups (capped at the item count)  */
+    int32_t rows_per_item; /* y rows per work item, 1..64 (default 8; in
+                              fa_decode_blocks without a plan 4 where more than
+                              the values are decoded)                           */
+    int32_t waves;         /* waves (64 lanes) per workgroup: 1, 2, 4, 8
+                              (default: one per row, up to 8)                   */
+    int32_t grid;          /* persistent workgroups (capped at the item count;
+                              default: one per item)                            */
     int32_t kernel;        /* 0 = separable VALU, 1 = MFMA (BF16/FP16 lattices;
                               16 rows x 64 columns per item and 4 waves: pass
                               rows_per_item 0 or 16 and waves 0 or 4)       */
     int32_t slab_floats;   /* LDS lattice slab, 4096..16384 floats (default 8192);
                               larger lattices are staged in x chunks            */
-    int32_t store;         /* 0 = non-temporal stores, 1 = ordinary stores
-                              (separable VALU kernel; the MFMA kernel writes
-                              partial lines and always stores ordinarily)    */
+    int32_t store;         /* 0 = non-temporal stores where a z row is whole
+                              128-byte lines, 1 = ordinary stores (separable
+                              VALU kernel; the MFMA kernel always stores
+                              ordinarily)                                    */
 } fa_tune;
 
 const char *fa_status_string(fa_status s);
@@ -423,8 +428,7 @@ fa_status fa_mse_loss(const double *sumsq, int32_t nblocks, double count, float 
  * stored).  grad equals fa_decode_blocks + fa_mse_grad bit for bit; sumsq
  * differs only in the order of its FP64 sum.  Runs the separable VALU
  * kernel (tune->kernel must be 0); tune, work, wg_off, ngroups as in
- * fa_decode_blocks, except that waves left at 0 (or a null tune) mean 8
- * here (one y row per wave at the default 8 rows per item).
+ * fa_decode_blocks, with 8 rows per item and 8 waves by default.
  *   samples, grad  device FP32 [nblocks][res0][res1][res2]
  *   sumsq          device FP64 [nblocks]
  *   workspace      device, fa_decode_residual_workspace(...) bytes (one

@@ -22,21 +22,21 @@ static __device__ __align__(256) double scratch[FA_NOALLOC_SCRATCH_BYTES / sizeo
 
 namespace {
 
-constexpr int kDefaultWaves = 4;
 constexpr int kDefaultRows = 8;
-constexpr int kDefaultGrid = 768;  // 256 CUs x 3 resident workgroups (LDS bound)
-// residual and error forms: one y row per wave by default (a wave that walks
-// several rows restages a large lattice's slab for each; at NCP 64 one row
-// per wave runs 2.5x faster)
-constexpr int kReduceWaves = 8;
+constexpr int kItemsWanted = 1024;  // workgroups of a decode: four per CU
 constexpr int kSearchPairs = 256;  // (block, candidate) pairs of an NCP search's launches
 
 struct Tune {
     int rows, waves, grid, kernel, slab, store;
 };
 
+// A wave per y row of an item, up to eight: a wave that walks several rows
+// has the slab wait for it (512 uneven blocks of 64^3, 8 rows: 8 waves 410 us,
+// 4 waves 458 us; NCP 64, error form: 2.5 times).
+int default_waves(int rows) { return rows >= 8 ? 8 : (rows >= 4 ? 4 : (rows >= 2 ? 2 : 1)); }
+
 Tune resolve(const fa_tune *t) {
-    Tune r{kDefaultRows, kDefaultWaves, 0, 0, kSlabDefault, 0};
+    Tune r{kDefaultRows, 0, 0, 0, kSlabDefault, 0};
     if (t && t->kernel == 1) r.rows = kMfmaRows;
     if (t) {
         if (t->rows_per_item > 0) r.rows = t->rows_per_item;
@@ -46,17 +46,15 @@ Tune resolve(const fa_tune *t) {
         if (t->slab_floats > 0) r.slab = t->slab_floats;
         r.store = t->store;
     }
+    if (r.waves == 0) r.waves = r.kernel == 1 ? 4 : default_waves(r.rows);
     return r;
 }
 
-// Default workgroup count: the separable VALU kernel runs persistently on
-// kDefaultGrid workgroups; the matrix-core kernel (two resident per CU, items
-// of very uneven length) runs one workgroup per item, which avoids the tail
-// of a persistent grid that does not divide the resident slots.
-int64_t default_grid(const Tune &t, int64_t items) {
-    if (t.grid > 0) return t.grid;
-    return t.kernel == 1 ? items : kDefaultGrid;
-}
+// Default workgroup count: one per item.  The hardware's dispatcher balances
+// items of uneven length; a persistent grid of 768 leaves a tail (512 uneven
+// blocks: 401 us against 390 us at 4 rows; 400 odd grids, values: 130 against
+// 95 us).
+int64_t default_grid(const Tune &t, int64_t items) { return t.grid > 0 ? t.grid : items; }
 
 int popcount4(uint32_t m) { return __builtin_popcount(m & 15u); }
 
@@ -100,9 +98,13 @@ DecodeLaunch grid_args(const fa_block *blocks, int32_t nblocks, const float *kno
     a.rows = t.rows;
     a.nrowt = (res[1] + t.rows - 1) / t.rows;
     a.ncolt = (res[2] + kWaveLanes - 1) / kWaveLanes;
+    a.xsegs = 1;
     a.nitems = (int64_t)nblocks * a.nrowt * a.ncolt;
     a.slab = t.slab;
-    a.nt_store = t.store == 0;
+    // non-temporal stores where every row is whole 128-byte lines; lines that
+    // two stores share go to memory twice otherwise (400 grids of 61 x 47 x 53,
+    // values: 107 us against 77 us)
+    a.nt_store = t.store == 0 && res[2] * 4 % 128 == 0;
     a.out = out;
     return a;
 }
@@ -157,8 +159,7 @@ fa_status decode_residual_impl(const fa_block *blocks, int32_t nblocks, const fl
     if ((work == nullptr) != (wg_off == nullptr)) return FA_ERR_INVALID_ARG;
     if (work && ngroups <= 0) return FA_ERR_INVALID_ARG;
     if (!res_supported(res)) return FA_ERR_UNSUPPORTED;
-    Tune t = resolve(tune);
-    if (!tune || tune->waves <= 0) t.waves = kReduceWaves;
+    const Tune t = resolve(tune);
     if (!tune_ok(t)) return FA_ERR_INVALID_ARG;
     if (t.kernel != 0) return FA_ERR_UNSUPPORTED;
     const int64_t need = (int64_t)nblocks * items_per_block(res, t) * (int64_t)sizeof(double);
@@ -327,12 +328,39 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     if ((work == nullptr) != (wg_off == nullptr)) return FA_ERR_INVALID_ARG;
     if (work && ngroups <= 0) return FA_ERR_INVALID_ARG;
     if (!res_supported(res)) return FA_ERR_UNSUPPORTED;
-    const Tune t = resolve(tune);
+    Tune t = resolve(tune);
+    const bool sep = t.kernel == 0, free_rows = !work && (!tune || tune->rows_per_item <= 0);
+    const int nch = popcount4(ch);
+    // Items are split along x where that pays (a segment's walk starts with
+    // p + 1 control planes of its own):
+    // - a large batch of three or four channels is bound by its stores, and
+    //   segments of 16 positions, eight rows each, leave the chip storing to
+    //   fewer, denser regions at a time: 384 uneven blocks of 64^3 as records
+    //   260 us, whole walks 285; planar, 512 blocks, 383 and 401.  From eight
+    //   rounds of workgroups on (four of eight waves to a CU): 40 blocks of
+    //   96 x 80 x 48, two rounds, took 52 us split and 39 whole.
+    // - few items leave CUs idle: down to eight positions a segment while
+    //   there are fewer than four workgroups per CU (1 block: 24 -> 11 us).
+    const int64_t eights = (int64_t)nblocks * ((res[1] + 7) / 8) * ((res[2] + kWaveLanes - 1) / kWaveLanes);
+    const bool dense = sep && t.grid == 0 && nch >= 3 && eights * (res[0] / 16) >= 8 * kItemsWanted;
+    // rows without a plan: four (512 uneven blocks, whole walks: 401 us, eight
+    // rows 408) but eight where a segment is short or there is one channel
+    // (400 grids of 61 x 47 x 53: 79 us, four rows 91)
+    if (sep && free_rows && nch > 1 && !dense) {
+        t.rows = 4;
+        if (!tune || tune->waves <= 0) t.waves = default_waves(t.rows);
+    }
     if (!tune_ok(t)) return FA_ERR_INVALID_ARG;
     DecodeLaunch a = grid_args(blocks, nblocks, knots, ctrl, dtype, res, ch, t, work, wg_off,
                                out);
     a.interleave = inter ? 1 : 0;
-    int grid = work ? ngroups : (int)std::min<int64_t>(a.nitems, default_grid(t, a.nitems));
+    if (sep && t.grid == 0)
+        a.xsegs = dense ? res[0] / 16
+                        : (int)std::max<int64_t>(1, std::min<int64_t>(kItemsWanted / a.nitems, res[0] / 8));
+    if (work && (int64_t)ngroups * a.xsegs > INT32_MAX) a.xsegs = 1;
+    a.nitems *= a.xsegs;
+    const int grid = work ? ngroups * a.xsegs
+                          : (int)std::min<int64_t>(a.nitems, default_grid(t, a.nitems));
     hipError_t e;
     if (t.kernel == 1) e = launch_decode_mfma(a, t.waves, grid, (hipStream_t)stream);
     else e = launch_decode_sep(a, t.waves, grid, (hipStream_t)stream);
@@ -691,8 +719,7 @@ fa_status fa_ncp_search(const float *samples, int32_t nblocks, const int32_t res
     double *xall = reinterpret_cast<double *>(w + L.pinv);
     const int ncand = ncp_hi - ncp_lo + 1;
     const int64_t stride = 2 * (int64_t)ncand;
-    Tune t = resolve(nullptr);
-    t.waves = kReduceWaves;
+    const Tune t = resolve(nullptr);
     const int64_t vox = (int64_t)res[0] * res[1] * res[2];
     const int per = (int)items_per_block(res, t);
     // every candidate's knots and pseudo-inverses depend on (n, p, res) only:

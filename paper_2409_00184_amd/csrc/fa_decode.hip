@@ -23,7 +23,7 @@
 //   (f - samples)^2 in FP64 per lane (x order), per wave (fixed shuffle
 //   tree) and per work item (waves in order) into one partial per item; a
 //   second kernel adds each block's partials in item order.  The samples
-//   are read one x position ahead through a buffer resource, and dead lanes
+//   are read four x positions ahead through a buffer resource, and dead lanes
 //   load and store at an offset outside every resource (no branch), so the
 //   x walk issues a fixed number of memory operations per step.
 // The error form (MODE 2) reads the samples the same way and stores nothing per
@@ -87,12 +87,21 @@ __device__ __forceinline__ float comp(const float4 &v, int r) {
 }
 
 // MODE 0: decode, 1: residual form, 2: error form, 3: decode of all four
-// channels stored interleaved (one 16-byte record per voxel)
+// channels stored interleaved (one 16-byte record per voxel), 4: decode of
+// the values alone
+//
+// The item's nrows x ncols columns are dealt to the lanes back to back, so
+// that narrow grids (ncols < 64) leave no lane idle but the last wave's.  The
+// walk covers x positions [ua, ub).  Every access of the walk goes through a
+// buffer resource with the lane's column in the vector offset (beyond the
+// resource for a lane without a column) and the x position and channel, always
+// inside, in the scalar offset, so a step spends no vector instruction on addresses: the
+// error form of 256 blocks of 64^3 went from 115 to 95 us.
 template <int P, bool NT, int MODE>
-__device__ void sep_item(const DecodeLaunch &a, int b, int row0, int nrows, int col0, int64_t item,
-                         SepSmem &sm) {
+__device__ void sep_item(const DecodeLaunch &a, int b, int row0, int nrows, int col0, int ua, int ub,
+                         int64_t item, SepSmem &sm) {
     const int tid = threadIdx.x, nthr = blockDim.x;
-    const int wave = tid >> 6, lane = tid & 63, nwaves = nthr >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, nwaves = nthr >> 6;
     const fa_block &B = a.blocks[b];
     const int nx = B.ncp[0], ny = B.ncp[1], nz = B.ncp[2];
     const int64_t koff = B.knot_off, coff = B.ctrl_off;
@@ -100,6 +109,8 @@ __device__ void sep_item(const DecodeLaunch &a, int b, int row0, int nrows, int 
     const int nkn = nx + ny + nz + 3 * (P + 1);
     constexpr bool RESID = MODE == 1 || MODE == 2;  // reads the samples
     constexpr bool GRAD = MODE == 1;   // stores the scaled residual
+    constexpr int kCpol = NT ? 2 : 0;  // buffer accesses: non-temporal
+    constexpr uint32_t kDead = 0x80000000u;  // beyond every resource
 
     lds_barrier();  // the previous item is done with the shared buffers
     for (int e = tid; e < nkn; e += nthr) sm.kn[e] = a.knots[koff + e];
@@ -108,32 +119,15 @@ __device__ void sep_item(const DecodeLaunch &a, int b, int row0, int nrows, int 
     const float *ty = tx + nx + P + 1;
     const float *tz = ty + ny + P + 1;
 
-    // x table: span and basis of every grid position along x
-    for (int u = tid; u < a.rx; u += nthr) {
-        const float uu = grid_pos(u, a.rx);
-        const int s = span_search(nx, P, tx, uu);
-        float N[P + 1], D[P + 1];
-        basis_ders<P>(tx, s, uu, N, D);
-        sm.xB[u] = pack4<P>(N);
-        sm.xD[u] = pack4<P>(D);
-        sm.xS[u] = s;
-    }
-
-    // lattice rows j in [jlo, jhi] cover the y windows of every row of the item
+    // control planes [i0, i1) cover the x windows of the item, lattice rows j
+    // in [jlo, jhi] its y windows
+    const int i0 = span_search(nx, P, tx, grid_pos(ua, a.rx)) - P;
+    const int i1 = span_search(nx, P, tx, grid_pos(ub - 1, a.rx)) + 1;
     const int jlo = span_search(ny, P, ty, grid_pos(row0, a.ry)) - P;
     const int jhi = span_search(ny, P, ty, grid_pos(row0 + nrows - 1, a.ry));
     const int plane = (jhi - jlo + 1) * nz;  // slab floats per x plane
-    const int ic = min(nx, sm.slab_floats / plane);
-    const bool single = (ic == nx);
-
-    // z basis of this lane's column
-    const bool wok = (col0 + lane) < a.rz;
-    const int w = wok ? col0 + lane : a.rz - 1;
-    const float zw = grid_pos(w, a.rz);
-    const int sz = span_search(nz, P, tz, zw);
-    float zB[P + 1], zD[P + 1];
-    basis_ders<P>(tz, sz, zw, zB, zD);
-    const int kz0 = sz - P;
+    const int ic = min(i1 - i0, sm.slab_floats / plane);
+    const bool single = (ic == i1 - i0);
 
     // Slab element e = ii * plane + r is value r of control plane c0 + ii's
     // rows jlo..jhi, which lie back to back in the lattice.  A thread walks
@@ -165,105 +159,114 @@ __device__ void sep_item(const DecodeLaunch &a, int b, int row0, int nrows, int 
                 if (e0 + q * nthr < cnt) sm.slab[e0 + q * nthr] = v[q];
         }
     };
+    if (single) stage(i0, i1);
 
-    lds_barrier();  // x table visible
-    if (single) {
-        stage(0, nx);
-        lds_barrier();
+    // x table: span and basis of the item's positions along x
+    for (int u = ua + tid; u < ub; u += nthr) {
+        const float uu = grid_pos(u, a.rx);
+        const int s = span_search(nx, P, tx, uu);
+        float N[P + 1], D[P + 1];
+        basis_ders<P>(tx, s, uu, N, D);
+        sm.xB[u] = pack4<P>(N);
+        if (!RESID && MODE != 4) sm.xD[u] = pack4<P>(D);
+        sm.xS[u] = s;
     }
+    lds_barrier();  // x table and slab visible
 
     const int64_t vox = (int64_t)a.rx * a.ry * a.rz;
-    const int64_t plane_out = (int64_t)a.ry * a.rz;
-    int64_t choff[4];
+    const uint32_t vb = (uint32_t)vox * 4u;
+    constexpr uint32_t rec = MODE == 3 ? 16u : 4u;  // bytes of a column's store
+    const uint32_t pstep = (uint32_t)(a.ry * a.rz) * rec;
+    double acc = 0.0;
+    float amax = 0.0f;
+    // this block's samples (residual and error form), and its output: the
+    // channels of the mask one after the other, or records
+    const __amdgpu_buffer_rsrc_t yr = make_rsrc(
+        RESID ? a.samples + (int64_t)(MODE == 2 ? b % a.nsrc : b) * vox : a.out, RESID ? vb : 0u);
+    const int nch = RESID || MODE == 4 ? 1 : a.nch;
+    const __amdgpu_buffer_rsrc_t orc =
+        make_rsrc(MODE == 2 ? nullptr : a.out + (int64_t)b * nch * vox,
+                  MODE == 2 ? 0u : (uint32_t)nch * vb);
+    uint32_t choff[4];
     {
-        int c = 0;
+        uint32_t c = 0;
+#pragma unroll
         for (int ch = 0; ch < 4; ++ch) {
-            choff[ch] = (int64_t)c * vox;
-            c += (a.mask >> ch) & 1u;
+            choff[ch] = c;
+            c += (a.mask >> ch) & 1u ? vb : 0u;
         }
     }
 
-    // residual form: samples and cotangent of this block through buffer
-    // resources (value channel only, so both have the layout [u][v][w])
-    constexpr uint32_t kDead = 0xfffffff0u;  // beyond every resource
-    double acc = 0.0;
-    float amax = 0.0f;
-    const __amdgpu_buffer_rsrc_t yr =
-        make_rsrc(RESID ? a.samples + (int64_t)(MODE == 2 ? b % a.nsrc : b) * vox : a.out, RESID ? (uint32_t)vox * 4u : 0u);
-    const __amdgpu_buffer_rsrc_t gr =
-        make_rsrc(GRAD ? a.out + (int64_t)b * vox : a.samples, GRAD ? (uint32_t)vox * 4u : 0u);
-
-    for (int rb = 0; rb < nrows; rb += nwaves) {
-        const int rr = rb + wave;
-        const bool rok = rr < nrows;
-        const int v = row0 + (rok ? rr : nrows - 1);
-        const float yv = grid_pos(v, a.ry);
-        const int sy = span_search(ny, P, ty, yv);
-        float yB[P + 1], yD[P + 1];
+    const int ncols = min(kWave, a.rz - col0), total = nrows * ncols;
+    for (int rb = kWave * wave; rb < (single ? total : ((total - 1) / (kWave * nwaves) + 1) * kWave * nwaves);
+         rb += kWave * nwaves) {
+        // this lane's column; a lane past the end repeats the last one, stores
+        // nothing and adds nothing
+        const bool live = rb + lane < total;
+        const int id = live ? rb + lane : total - 1;
+        const int rr = id / ncols;
+        const int v = row0 + rr, w = col0 + id - rr * ncols;
+        const float zw = grid_pos(w, a.rz), yv = grid_pos(v, a.ry);
+        const int sz = span_search(nz, P, tz, zw), sy = span_search(ny, P, ty, yv);
+        float zB[P + 1], zD[P + 1], yB[P + 1], yD[P + 1];
+        basis_ders<P>(tz, sz, zw, zB, zD);
         basis_ders<P>(ty, sy, yv, yB, yD);
-        const int jrow = sy - P - jlo;
-
-        float *ob = a.out + (int64_t)b * a.nch * vox + (int64_t)v * a.rz + w;
-        const bool live = rok && wok;
-        const uint32_t col_off = ((uint32_t)v * (uint32_t)a.rz + (uint32_t)w) * 4u;
-        const uint32_t pstep = (uint32_t)plane_out * 4u;
+        const int sl0 = (sy - P - jlo) * nz + sz - P;
+        const uint32_t col = live ? ((uint32_t)v * (uint32_t)a.rz + (uint32_t)w) * rec : kDead;
 
       // the x walk, specialised on whether the slab holds every control
       // plane (then it stages nothing inside the walk)
       auto walk = [&](auto single_c) {
         constexpr bool SINGLE = decltype(single_c)::value;
-        int clo = 0, chi = SINGLE ? nx : ic;
+        int clo = i0, chi = SINGLE ? i1 : i0 + ic;
         if (!SINGLE) {
             lds_barrier();
-            stage(0, ic);
+            stage(clo, chi);
             lds_barrier();
         }
 
         float wBB[P + 1], wDB[P + 1], wBD[P + 1];
 #pragma unroll
         for (int r = 0; r <= P; ++r) wBB[r] = wDB[r] = wBD[r] = 0.0f;
-        int top = -1;
-        // residual form: the sample of x position u, loaded four positions
-        // ahead into one of four registers used in turn (no register copy
-        // waits for a load in flight)
+        int top = i0 - 1;
+        // the sample of x position u (the last one again past the end), loaded
+        // four positions ahead into one of four registers used in turn (no
+        // register copy waits for a load in flight)
         auto yload = [&](int u) {
             return RESID ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                         yr, (live && u < a.rx)
-                                                                 ? col_off + (uint32_t)u * pstep
-                                                                 : kDead,
-                                                         0, 0))
+                                                         yr, col, (uint32_t)min(u, ub - 1) * pstep, 0))
                          : 0.0f;
         };
         // issue order load, store, load, store as in every step, so the
         // counter wait at a step is the same on entry as in the loop (the
         // stores go beyond the resource and are dropped)
         auto ydummy = [&]() {
-            if (GRAD) __builtin_amdgcn_raw_buffer_store_b32(0u, gr, kDead, 0, 0);
+            if (GRAD) __builtin_amdgcn_raw_buffer_store_b32(0u, orc, kDead, 0, 0);
         };
         float y0 = 0.0f, y1 = 0.0f, y2 = 0.0f, y3 = 0.0f;
         if constexpr (RESID) {
-            y0 = yload(0);
+            y0 = yload(ua);
             ydummy();
-            y1 = yload(1);
+            y1 = yload(ua + 1);
             ydummy();
-            y2 = yload(2);
+            y2 = yload(ua + 2);
             ydummy();
-            y3 = yload(3);
+            y3 = yload(ua + 3);
             ydummy();
         }
 
         auto step = [&](int u, float &ycur) {
-            const int s = sm.xS[u];
+            const int s = __builtin_amdgcn_readfirstlane(sm.xS[u]);
             while (top < s) {  // uniform over the workgroup
                 ++top;
                 if (!SINGLE && top >= chi) {
                     lds_barrier();
                     clo = chi;
-                    chi = min(clo + ic, nx);
+                    chi = min(clo + ic, i1);
                     stage(clo, chi);
                     lds_barrier();
                 }
-                const float *sl = sm.slab + (top - clo) * plane + jrow * nz + kz0;
+                const float *sl = sm.slab + (top - clo) * plane + sl0;
                 float tB[P + 1], tD[P + 1];
 #pragma unroll
                 for (int jj = 0; jj <= P; ++jj) {
@@ -295,7 +298,7 @@ __device__ void sep_item(const DecodeLaunch &a, int b, int row0, int nrows, int 
                 wBD[P] = uBD;
             }
             const float4 bx = sm.xB[u];
-            const float4 dx = sm.xD[u];
+            const float4 dx = RESID || MODE == 4 ? bx : sm.xD[u];
             float val = 0.0f, gx = 0.0f, gy = 0.0f, gz = 0.0f;
 #pragma unroll
             for (int r = 0; r <= P; ++r) {
@@ -305,59 +308,49 @@ __device__ void sep_item(const DecodeLaunch &a, int b, int row0, int nrows, int 
                 gy = fmaf(cb, wDB[r], gy);
                 gz = fmaf(cb, wBD[r], gz);
             }
+            const uint32_t at = (uint32_t)u * pstep;
+            auto put = [&](float x, uint32_t ch) {
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), orc, col, at + ch, kCpol);
+            };
             if (RESID) {
                 // use the sample before the register is reloaded, so the
                 // old and new values never live at once (no copy)
-                const float r = val - ycur;
-                const uint32_t off = col_off + (uint32_t)u * pstep;
+                const float r = live ? val - ycur : 0.0f;
                 ycur = yload(u + 4);
-                const double rd = live ? (double)r : 0.0;
-                acc = fma(rd, rd, acc);
-                if (GRAD)
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, r * a.gscale),
-                                                          gr, live ? off : kDead, 0, NT ? 2 : 0);
-                else
-                    amax = fmaxf(amax, live ? fabsf(r) : 0.0f);
+                acc = fma((double)r, (double)r, acc);
+                if (GRAD) put(r * a.gscale, 0);
+                else amax = fmaxf(amax, fabsf(r));
             } else if (MODE == 3) {
-                if (live) {
-                    const f32x4 rec = {val, gx, gy, gz};
-                    f32x4 *o = reinterpret_cast<f32x4 *>(a.out) +
-                               ((int64_t)b * vox + (int64_t)u * plane_out + (int64_t)v * a.rz + w);
-                    if (NT) __builtin_nontemporal_store(rec, o);
-                    else *o = rec;
-                }
-            } else if (live) {
-                float *o = ob + (int64_t)u * plane_out;
-                if (NT) {
-                    if (a.mask & 1u) __builtin_nontemporal_store(val, o + choff[0]);
-                    if (a.mask & 2u) __builtin_nontemporal_store(gx, o + choff[1]);
-                    if (a.mask & 4u) __builtin_nontemporal_store(gy, o + choff[2]);
-                    if (a.mask & 8u) __builtin_nontemporal_store(gz, o + choff[3]);
-                } else {
-                    if (a.mask & 1u) o[choff[0]] = val;
-                    if (a.mask & 2u) o[choff[1]] = gx;
-                    if (a.mask & 4u) o[choff[2]] = gy;
-                    if (a.mask & 8u) o[choff[3]] = gz;
-                }
+                typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+                const u32x4 d = {__float_as_uint(val), __float_as_uint(gx), __float_as_uint(gy),
+                                 __float_as_uint(gz)};
+                __builtin_amdgcn_raw_buffer_store_b128(d, orc, col, at, kCpol);
+            } else if (MODE == 4) {
+                put(val, 0);
+            } else {
+                if (a.mask & 1u) put(val, choff[0]);
+                if (a.mask & 2u) put(gx, choff[1]);
+                if (a.mask & 4u) put(gy, choff[2]);
+                if (a.mask & 8u) put(gz, choff[3]);
             }
         };
-        int u = 0;
+        int u = ua;
         if constexpr (RESID) {
-            for (; u + 3 < a.rx; u += 4) {
+            for (; u + 3 < ub; u += 4) {
                 step(u, y0);
                 step(u + 1, y1);
                 step(u + 2, y2);
                 step(u + 3, y3);
             }
-            if (u < a.rx) step(u, y0);
-            if (u + 1 < a.rx) step(u + 1, y1);
-            if (u + 2 < a.rx) step(u + 2, y2);
+            if (u < ub) step(u, y0);
+            if (u + 1 < ub) step(u + 1, y1);
+            if (u + 2 < ub) step(u + 2, y2);
         } else {  // no samples: two steps per iteration keep the code small
-            for (; u + 1 < a.rx; u += 2) {
+            for (; u + 1 < ub; u += 2) {
                 step(u, y0);
                 step(u + 1, y1);
             }
-            if (u < a.rx) step(u, y0);
+            if (u < ub) step(u, y0);
         }
       };
         if (single) walk(std::true_type{});
@@ -401,9 +394,12 @@ __global__ __launch_bounds__(WAVES * 64) void decode_sep_kernel(DecodeLaunch a) 
     SepSmem sm = carve(dyn_lds, a.rx, a.slab);
     const int wg = xcd_order(blockIdx.x, gridDim.x);
     int64_t beg, end, step;
-    if (a.work) {
-        beg = a.wg_off[wg];
-        end = a.wg_off[wg + 1];
+    int seg = 0;
+    if (a.work) {  // xsegs workgroups run a plan's group, one x segment each
+        const int group = wg / a.xsegs;
+        seg = wg - group * a.xsegs;
+        beg = a.wg_off[group];
+        end = a.wg_off[group + 1];
         step = 1;
     } else {
         beg = wg;
@@ -420,18 +416,23 @@ __global__ __launch_bounds__(WAVES * 64) void decode_sep_kernel(DecodeLaunch a) 
             nrows = wk.nrows;
             col0 = wk.col0;
         } else {
-            b = (int)(it / per);
-            const int r = (int)(it - (int64_t)b * per);
+            // a tile's x segments in a row (a block's tiles of one segment in a
+            // row: 270 us against 260 for 384 uneven blocks, records)
+            const int64_t t = it / a.xsegs;
+            seg = (int)(it - t * a.xsegs);
+            b = (int)(t / per);
+            const int r = (int)(t - (int64_t)b * per);
             row0 = (r / a.ncolt) * a.rows;
             nrows = min(a.rows, a.ry - row0);
             col0 = (r % a.ncolt) * kWave;
         }
+        const int ua = seg * a.rx / a.xsegs, ub = (seg + 1) * a.rx / a.xsegs;
         // the item's index in the default order, whatever order runs it
         const int64_t item = (int64_t)b * per + (row0 / a.rows) * a.ncolt + col0 / kWave;
         const int p = a.blocks[b].degree[0];
-        if (p == 3) sep_item<3, NT, MODE>(a, b, row0, nrows, col0, item, sm);
-        else if (p == 2) sep_item<2, NT, MODE>(a, b, row0, nrows, col0, item, sm);
-        else sep_item<1, NT, MODE>(a, b, row0, nrows, col0, item, sm);
+        if (p == 3) sep_item<3, NT, MODE>(a, b, row0, nrows, col0, ua, ub, item, sm);
+        else if (p == 2) sep_item<2, NT, MODE>(a, b, row0, nrows, col0, ua, ub, item, sm);
+        else sep_item<1, NT, MODE>(a, b, row0, nrows, col0, ua, ub, item, sm);
     }
 }
 
@@ -559,6 +560,9 @@ hipError_t launch_decode_sep(const DecodeLaunch &a, int waves, int grid, hipStre
     if (a.interleave)
         return a.nt_store ? launch_sep<true, 3>(a, waves, grid, s)
                           : launch_sep<false, 3>(a, waves, grid, s);
+    if (!a.samples && a.mask == 1u)
+        return a.nt_store ? launch_sep<true, 4>(a, waves, grid, s)
+                          : launch_sep<false, 4>(a, waves, grid, s);
     if (a.samples)
         return a.nt_store ? launch_sep<true, 1>(a, waves, grid, s)
                           : launch_sep<false, 1>(a, waves, grid, s);
