@@ -30,20 +30,24 @@ HBM_PEAK_GBS = 8000.0
 METRIC = "decoded voxels/sec (value+grad), batched vs plain, % HBM/MFMA roofline"
 KERNEL_SOURCES = {
     "decode_sep": ["paper_2409_00184_amd/csrc/fa_decode.hip",
+                   "paper_2409_00184_amd/csrc/fa_sep.hpp",
                    "paper_2409_00184_amd/csrc/fa_device.hpp"],
     "query": ["paper_2409_00184_amd/csrc/fa_query.hip", "paper_2409_00184_amd/csrc/fa_eval.hpp",
               "paper_2409_00184_amd/csrc/fa_device.hpp"],
     "decode_mfma": ["paper_2409_00184_amd/csrc/fa_mfma.hip",
+                    "paper_2409_00184_amd/csrc/fa_sep.hpp",
                     "paper_2409_00184_amd/csrc/fa_device.hpp"],
     "adjoint": ["paper_2409_00184_amd/csrc/fa_adjoint.hip",
                 "paper_2409_00184_amd/csrc/fa_device.hpp"],
     "ncp_search": ["paper_2409_00184_amd/csrc/fa_fit.hip",
                    "paper_2409_00184_amd/csrc/fa_decode.hip",
+                   "paper_2409_00184_amd/csrc/fa_sep.hpp",
                    "paper_2409_00184_amd/csrc/fa_device.hpp"],
     "fit": ["paper_2409_00184_amd/csrc/fa_fit.hip", "paper_2409_00184_amd/csrc/fa_device.hpp"],
     "fit_decode": ["paper_2409_00184_amd/csrc/fa_fit.hip",
                    "paper_2409_00184_amd/csrc/fa_adjoint.hip",
                    "paper_2409_00184_amd/csrc/fa_decode.hip",
+                   "paper_2409_00184_amd/csrc/fa_sep.hpp",
                    "paper_2409_00184_amd/csrc/fa_device.hpp"],
     "render": ["paper_2409_00184_amd/csrc/fa_render.hip", "paper_2409_00184_amd/csrc/fa_eval.hpp",
                "paper_2409_00184_amd/csrc/fa_device.hpp"],

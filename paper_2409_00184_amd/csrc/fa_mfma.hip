@@ -35,14 +35,13 @@
 // record per voxel) the same LDS tile holds the item's 16 x 64 records
 // instead, and each store instruction writes one whole z row (1 KB).
 // Items the tile does not take (NCP_z > 32, or a y window of more than 16
-// lattice rows) are decoded voxel by voxel by the same workgroup.
+// lattice rows) take the separable vector form in the same workgroup.
 //
 // Operand layouts (checked on the device):
 //   v_mfma_f32_16x16x32: lane l holds A[l%16][8(l/16)+e], B[8(l/16)+e][l%16], e < 8
 //   v_mfma_f32_16x16x16: lane l holds A[l%16][4(l/16)+e], B[4(l/16)+e][l%16], e < 4
 //   both: lane l receives D[4(l/16)+r][l%16], r < 4.
-#include "fa_device.hpp"
-#include "fa_internal.hpp"
+#include "fa_sep.hpp"
 
 namespace fa {
 namespace {
@@ -163,64 +162,9 @@ __device__ __forceinline__ MSmem mcarve(void *base, int rx) {
     return s;
 }
 
-// Voxel-by-voxel decode of one item (items the tile does not take).
-template <int P, bool INTER>
-__device__ void direct_item(const DecodeLaunch &a, const fa_block &B, int b, int row0, int nrows,
-                            int col0) {
-    const int nx = B.ncp[0], ny = B.ncp[1], nz = B.ncp[2];
-    const float *tx = a.knots + B.knot_off;
-    const float *ty = tx + nx + P + 1;
-    const float *tz = ty + ny + P + 1;
-    const int ncol = min(kWave, a.rz - col0);
-    const int64_t vox = (int64_t)a.rx * a.ry * a.rz;
-    const int total = a.rx * nrows * ncol;
-    for (int e = threadIdx.x; e < total; e += blockDim.x) {
-        const int w = col0 + e % ncol;
-        const int v = row0 + (e / ncol) % nrows;
-        const int u = e / (ncol * nrows);
-        const float pu = grid_pos(u, a.rx), pv = grid_pos(v, a.ry), pw = grid_pos(w, a.rz);
-        const int su = span_search(nx, P, tx, pu), sv = span_search(ny, P, ty, pv),
-                  sw = span_search(nz, P, tz, pw);
-        float xB[P + 1], xD[P + 1], yB[P + 1], yD[P + 1], zB[P + 1], zD[P + 1];
-        basis_ders<P>(tx, su, pu, xB, xD);
-        basis_ders<P>(ty, sv, pv, yB, yD);
-        basis_ders<P>(tz, sw, pw, zB, zD);
-        float r[4] = {0, 0, 0, 0};
-        const int64_t base = B.ctrl_off + ((int64_t)(su - P) * ny + (sv - P)) * nz + (sw - P);
-#pragma unroll 1
-        for (int i = 0; i <= P; ++i) {
-#pragma unroll 1
-            for (int j = 0; j <= P; ++j) {
-                const int64_t row = base + ((int64_t)i * ny + j) * nz;
-                float tB = 0.0f, tD = 0.0f;
-#pragma unroll
-                for (int k = 0; k <= P; ++k) {
-                    const float c = load_ctrl(a.ctrl, a.dtype, row + k, B.scale);
-                    tB = fmaf(zB[k], c, tB);
-                    tD = fmaf(zD[k], c, tD);
-                }
-                r[0] = fmaf(xB[i] * yB[j], tB, r[0]);
-                r[1] = fmaf(xD[i] * yB[j], tB, r[1]);
-                r[2] = fmaf(xB[i] * yD[j], tB, r[2]);
-                r[3] = fmaf(xB[i] * yB[j], tD, r[3]);
-            }
-        }
-        const int64_t vi = ((int64_t)u * a.ry + v) * a.rz + w;
-        if constexpr (INTER) {
-            const f32x4v rec = {r[0], r[1], r[2], r[3]};
-            reinterpret_cast<f32x4v *>(a.out)[(int64_t)b * vox + vi] = rec;
-            continue;
-        }
-        float *o = a.out + (int64_t)b * a.nch * vox + vi;
-        int c = 0;
-        for (int ch = 0; ch < 4; ++ch)
-            if ((a.mask >> ch) & 1u) o[(int64_t)(c++) * vox] = r[ch];
-    }
-}
-
 template <int DT, int P, bool INTER>
 __device__ void mfma_item(const DecodeLaunch &a, const fa_block &B, int b, int row0, int nrows,
-                          int col0, const MSmem &sm) {
+                          int col0, int ua, int ub, const MSmem &sm) {
     const int tid = threadIdx.x, q = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, l16 = lane & 15;
     const int nx = B.ncp[0], ny = B.ncp[1], nz = B.ncp[2];
@@ -234,14 +178,19 @@ __device__ void mfma_item(const DecodeLaunch &a, const fa_block &B, int b, int r
     const int jlo = span_search(ny, P, ty, grid_pos(row0, a.ry)) - P;
     const int jhi = span_search(ny, P, ty, grid_pos(row0 + nrows - 1, a.ry));
     if (nz > kK || jhi - jlo + 1 > kJ) {
-        direct_item<P, INTER>(a, B, b, row0, nrows, col0);
+        // the vector form, its slab where the fragments and tiles would be
+        // (300 grids of 61 x 47 x 53, a third of them NCP_z 40: 411 us; voxel
+        // by voxel, as it was, 2138)
+        SepSmem ss{sm.xB, sm.xD, sm.xS, sm.kn, reinterpret_cast<float *>(sm.frag),
+                   kStage * kWave * 4 + 4 * kRows * 16 * 4};
+        sep_item<P, false, INTER ? 3 : 0>(a, b, row0, nrows, col0, ua, ub, 0, ss);
         return;
     }
 
     // x table: span and scale * basis, the coefficient of plane s-P+r in
     // ring slot (s-P+r) mod (P+1)
     const float scale = B.scale;
-    for (int u = tid; u < a.rx; u += blockDim.x) {
+    for (int u = ua + tid; u < ub; u += blockDim.x) {
         const float pu = grid_pos(u, a.rx);
         const int s = span_search(nx, P, tx, pu);
         float N[P + 1], D[P + 1];
@@ -341,15 +290,17 @@ __device__ void mfma_item(const DecodeLaunch &a, const fa_block &B, int b, int r
     const __amdgpu_buffer_rsrc_t orc =
         make_rsrc(a.out + (int64_t)b * a.nch * vox, (uint32_t)a.nch * vox * 4u);
     const uint32_t plane_b = (uint32_t)a.ry * (uint32_t)a.rz * 4u;
-    uint32_t vo = ((uint32_t)(row0 + srow) * (uint32_t)a.rz + (uint32_t)ws) * 4u;
+    uint32_t vo = ((uint32_t)(row0 + srow) * (uint32_t)a.rz + (uint32_t)ws) * 4u +
+                  (uint32_t)ua * plane_b;
     // interleaved: this lane writes records (l16, 16q + 4g + r) at column
     // slot col ^ l16 (the 16 lanes of a row group hit 16 bank groups), and
     // wave q stores rows 4q .. 4q+3, lane = column, 16 bytes each
     const __amdgpu_buffer_rsrc_t irc =
         make_rsrc(reinterpret_cast<f32x4v *>(a.out) + (int64_t)b * vox, vox * 16u);
     const bool iok = col0 + lane < a.rz;
-    uint32_t io = ((uint32_t)row0 * (uint32_t)a.rz + (uint32_t)(col0 + lane)) * 16u;
     const uint32_t irow_b = (uint32_t)a.rz * 16u, iplane_b = (uint32_t)a.ry * irow_b;
+    uint32_t io = ((uint32_t)row0 * (uint32_t)a.rz + (uint32_t)(col0 + lane)) * 16u +
+                  (uint32_t)ua * iplane_b;
     uint32_t choff[4];
     {
         uint32_t c = 0;
@@ -367,16 +318,19 @@ __device__ void mfma_item(const DecodeLaunch &a, const fa_block &B, int b, int r
     // quarter of the planes, every wave reads all of them; the x walk then
     // touches no global memory but its stores (a global load in the walk
     // would make each new plane wait for every store issued before it)
-    int clo = 0;
+    // (planes from the first that the item's positions touch)
+    const int i0 = span_search(nx, P, tx, grid_pos(ua, a.rx)) - P;
+    const int i1 = span_search(nx, P, tx, grid_pos(ub - 1, a.rx)) + 1;
+    int clo = i0;
     auto stage = [&](int c0) {
-        const int c1 = min(nx, c0 + kStage);
+        const int c1 = min(i1, c0 + kStage);
         for (int i = c0 + q; i < c1; i += 4) sm.frag[(i - c0) * kWave + lane] = load_frag(i);
     };
-    stage(0);
-    int top = -1;
+    stage(i0);
+    int top = i0 - 1;
     lds_barrier();  // x table and fragments visible
 
-    for (int u = 0; u < a.rx; ++u) {
+    for (int u = ua; u < ub; ++u) {
         const int s = __builtin_amdgcn_readfirstlane(sm.xS[u]);
         while (top < s) {  // uniform: the next control plane enters the ring
             ++top;
@@ -481,9 +435,12 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(DecodeLaunch a) {
     const MSmem sm = mcarve(dyn_lds, a.rx);
     const int wg = xcd_order(blockIdx.x, gridDim.x);
     int64_t beg, end, step;
-    if (a.work) {
-        beg = a.wg_off[wg];
-        end = a.wg_off[wg + 1];
+    int seg = 0;
+    if (a.work) {  // xsegs workgroups run a plan's group, one x segment each
+        const int group = wg / a.xsegs;
+        seg = wg - group * a.xsegs;
+        beg = a.wg_off[group];
+        end = a.wg_off[group + 1];
         step = 1;
     } else {
         beg = wg;
@@ -500,17 +457,20 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(DecodeLaunch a) {
             nrows = wk.nrows;
             col0 = wk.col0;
         } else {
-            b = (int)(it / per);
-            const int r = (int)(it - (int64_t)b * per);
+            const int64_t t = it / a.xsegs;  // a tile's x segments in a row
+            seg = (int)(it - t * a.xsegs);
+            b = (int)(t / per);
+            const int r = (int)(t - (int64_t)b * per);
             row0 = (r / a.ncolt) * a.rows;
             nrows = min(a.rows, a.ry - row0);
             col0 = (r % a.ncolt) * kWave;
         }
+        const int ua = seg * a.rx / a.xsegs, ub = (seg + 1) * a.rx / a.xsegs;
         const fa_block &B = a.blocks[b];
         const int p = B.degree[0];
-        if (p == 3) mfma_item<DT, 3, INTER>(a, B, b, row0, nrows, col0, sm);
-        else if (p == 2) mfma_item<DT, 2, INTER>(a, B, b, row0, nrows, col0, sm);
-        else mfma_item<DT, 1, INTER>(a, B, b, row0, nrows, col0, sm);
+        if (p == 3) mfma_item<DT, 3, INTER>(a, B, b, row0, nrows, col0, ua, ub, sm);
+        else if (p == 2) mfma_item<DT, 2, INTER>(a, B, b, row0, nrows, col0, ua, ub, sm);
+        else mfma_item<DT, 1, INTER>(a, B, b, row0, nrows, col0, ua, ub, sm);
     }
 }
 
