@@ -329,6 +329,7 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     if (work && ngroups <= 0) return FA_ERR_INVALID_ARG;
     if (!res_supported(res)) return FA_ERR_UNSUPPORTED;
     Tune t = resolve(tune);
+    if (!tune_ok(t)) return FA_ERR_INVALID_ARG;
     const bool sep = t.kernel == 0, free_rows = !work && (!tune || tune->rows_per_item <= 0);
     const int nch = popcount4(ch);
     // Items are split along x where that pays (a segment's walk starts with
@@ -336,13 +337,16 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     // - a large batch of three or four channels is bound by its stores, and
     //   segments of 16 positions, eight rows each, leave the chip storing to
     //   fewer, denser regions at a time: 384 uneven blocks of 64^3 as records
-    //   260 us, whole walks 285; planar, 512 blocks, 383 and 401.  From eight
+    //   260 us, whole walks 285 (four rows each: 291); planar, 512 blocks, 383
+    //   and 401 (444).  From eight
     //   rounds of workgroups on (four of eight waves to a CU): 40 blocks of
     //   96 x 80 x 48, two rounds, took 52 us split and 39 whole.
     // - few items leave CUs idle: down to eight positions a segment while
     //   there are fewer than four workgroups per CU (1 block: 24 -> 11 us).
-    const int64_t eights = (int64_t)nblocks * ((res[1] + 7) / 8) * ((res[2] + kWaveLanes - 1) / kWaveLanes);
-    const bool dense = sep && t.grid == 0 && nch >= 3 && eights * (res[0] / 16) >= 8 * kItemsWanted;
+    // A persistent grid (fewer workgroups than items) runs whole items.
+    const bool each = t.grid <= 0 || t.grid >= nblocks * items_per_block(res, t);
+    const bool dense = sep && each && nch >= 3 && t.rows >= 8 &&
+                       nblocks * items_per_block(res, t) * (res[0] / 16) >= 8 * kItemsWanted;
     // rows without a plan: four (512 uneven blocks, whole walks: 401 us, eight
     // rows 408) but eight where a segment is short or there is one channel
     // (400 grids of 61 x 47 x 53: 79 us, four rows 91)
@@ -350,20 +354,19 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
         t.rows = 4;
         if (!tune || tune->waves <= 0) t.waves = default_waves(t.rows);
     }
-    if (!tune_ok(t)) return FA_ERR_INVALID_ARG;
     DecodeLaunch a = grid_args(blocks, nblocks, knots, ctrl, dtype, res, ch, t, work, wg_off,
                                out);
     a.interleave = inter ? 1 : 0;
     // - the matrix-core decode, two workgroups to a CU, gains from filling the
     //   chip only (1 block: 65 -> 16 us; 128 blocks in halves 142 us, whole 119)
-    if (t.grid == 0) {
+    if (each) {
         const int64_t fill = (sep ? kItemsWanted : kItemsWanted / 2) / a.nitems;
         a.xsegs = dense ? res[0] / 16 : (int)std::max<int64_t>(1, std::min<int64_t>(fill, res[0] / 8));
     }
     if (work && (int64_t)ngroups * a.xsegs > INT32_MAX) a.xsegs = 1;
     a.nitems *= a.xsegs;
     const int grid = work ? ngroups * a.xsegs
-                          : (int)std::min<int64_t>(a.nitems, default_grid(t, a.nitems));
+                          : (int)std::min<int64_t>(a.nitems, each ? a.nitems : t.grid);
     hipError_t e;
     if (t.kernel == 1) e = launch_decode_mfma(a, t.waves, grid, (hipStream_t)stream);
     else e = launch_decode_sep(a, t.waves, grid, (hipStream_t)stream);

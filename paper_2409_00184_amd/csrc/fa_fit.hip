@@ -234,7 +234,7 @@ __device__ __forceinline__ const double *fit_x_of(const FitArgs &a, int bi) {
     return a.X + (bi / a.nsrc) * a.xcand + (bi % a.nsrc) * a.xstride;
 }
 
-constexpr uint32_t kDeadFit = 0x40000000u;      // offset beyond every buffer (also twice)
+constexpr uint32_t kDeadFit = 0x40000000u;      // offset beyond every buffer (also two or three times)
 constexpr int kZyWaves = 4;                     // waves per fit_zy workgroup
 constexpr int kOpSteps = kFitR / 4;             // K steps of a 64-long contraction
 constexpr int kOpTile = kOpSteps * kWave;       // doubles of one 16-row operand table
@@ -351,9 +351,9 @@ __device__ __forceinline__ void fit_zy_block(const FitArgs &a, int bi, int x0, i
     int x = x0 + wave;
     if (x < x1) load((uint32_t)x * slice, cur);
     for (; x < x1; x += kZyWaves) {
-        // the next slice (at the end the last one again), in flight during all
-        // of this one
-        load((uint32_t)(x + kZyWaves < x1 ? x + kZyWaves : x) * slice, nxt);
+        // the next slice, in flight during all of this one (after the last one
+        // nothing: the vector offset is dead)
+        load(x + kZyWaves < x1 ? (uint32_t)(x + kZyWaves) * slice : kDeadFit, nxt);
         trim(cur);
         fit_zy_slice<NT, NJ>(oz, oy, cur, nq, nk, ny, nz, lane, U, (uint32_t)x * ub);
 #pragma unroll
@@ -369,8 +369,9 @@ __global__ __launch_bounds__(kZyWaves * 64, 2) void fit_zy_kernel(FitArgs a, int
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int tid = threadIdx.x;
     const int groups = (a.r0 + xgroup - 1) / xgroup;
-    const int bi = (int)(blockIdx.x / groups);
-    const int x0 = (int)(blockIdx.x - (int64_t)bi * groups) * xgroup;
+    // a block's groups on one XCD: its L2 then holds their pseudo-inverses
+    const int wg = xcd_order(blockIdx.x, gridDim.x), bi = wg / groups;
+    const int x0 = (wg - bi * groups) * xgroup;
     const int x1 = min(a.r0, x0 + xgroup);
     const fa_block &b = a.blocks[bi];
     const int ny = uni32(b.ncp[1]), nz = uni32(b.ncp[2]);
@@ -456,8 +457,8 @@ __device__ __forceinline__ void fit_x_tiles(const FitArgs &a, int t0, int t1, in
 __global__ __launch_bounds__(kFxWaves * 64) void fit_x_kernel(FitArgs a, int echunks, int tchunk) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int tid = threadIdx.x;
-    const int bi = (int)(blockIdx.x / echunks);
-    const int t0 = (int)(blockIdx.x - (int64_t)bi * echunks) * tchunk;
+    const int wg = xcd_order(blockIdx.x, gridDim.x), bi = wg / echunks;
+    const int t0 = (wg - bi * echunks) * tchunk;
     const fa_block &b = a.blocks[bi];
     const int nx = uni32(b.ncp[0]), ny = uni32(b.ncp[1]), nz = uni32(b.ncp[2]);
     const int ne = ny * nz, t1 = min(t0 + tchunk, (ne + 15) >> 4);
