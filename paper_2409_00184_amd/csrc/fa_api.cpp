@@ -54,7 +54,13 @@ Tune resolve(const fa_tune *t) {
 // items of uneven length; a persistent grid of 768 leaves a tail (512 uneven
 // blocks: 401 us against 390 us at 4 rows; 400 odd grids, values: 130 against
 // 95 us).
-int64_t default_grid(const Tune &t, int64_t items) { return t.grid > 0 ? t.grid : items; }
+// At most kMostGroups, which a launch of 512 threads each can hold; the groups
+// then take several items.
+constexpr int64_t kMostGroups = 1 << 20;
+
+int64_t default_grid(const Tune &t, int64_t items) {
+    return t.grid > 0 ? t.grid : std::min(items, kMostGroups);
+}
 
 int popcount4(uint32_t m) { return __builtin_popcount(m & 15u); }
 
@@ -363,10 +369,10 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
         const int64_t fill = (sep ? kItemsWanted : kItemsWanted / 2) / a.nitems;
         a.xsegs = dense ? res[0] / 16 : (int)std::max<int64_t>(1, std::min<int64_t>(fill, res[0] / 8));
     }
-    if (work && (int64_t)ngroups * a.xsegs > INT32_MAX) a.xsegs = 1;
+    if (work && (int64_t)ngroups * a.xsegs > kMostGroups) a.xsegs = 1;
     a.nitems *= a.xsegs;
     const int grid = work ? ngroups * a.xsegs
-                          : (int)std::min<int64_t>(a.nitems, each ? a.nitems : t.grid);
+                          : (int)std::min<int64_t>(a.nitems, each ? kMostGroups : t.grid);
     hipError_t e;
     if (t.kernel == 1) e = launch_decode_mfma(a, t.waves, grid, (hipStream_t)stream);
     else e = launch_decode_sep(a, t.waves, grid, (hipStream_t)stream);
