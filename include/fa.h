@@ -291,9 +291,9 @@ fa_status fa_render_rays(const fa_block *blocks, int32_t nblocks, const int32_t 
  * fit of the lattice to samples y on the block's grid, this is the fit's
  * gradient: the step model(NCP, degree) of Alg. 1 (Sec. 4.2.1) solves that
  * fit for every candidate NCP.  Deterministic (fixed summation order, no
- * floating-point atomics).  Runs on the FP32 matrix cores, whose products
- * include zero weights: an infinite or NaN cotangent value makes the
- * gradient of its whole block NaN, not only that of its window.
+ * floating-point atomics; the order depends on res, mask and nblocks).  An
+ * infinite or NaN cotangent value reaches the lattice values whose basis
+ * window holds its grid position, and no others.
  *   grad_out   device FP32 [nblocks][popcount(mask)][res0][res1][res2]
  *   grad_ctrl  device FP32 lattice layout (same offsets as ctrl); the
  *              lattices of the blocks are overwritten, other elements are

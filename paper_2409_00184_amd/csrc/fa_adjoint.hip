@@ -90,6 +90,7 @@ struct AmSmem<false> {
     int zs[kAM];
     int tw[2][kAM / 16];  // first and last w with a basis entry in each k tile
     float lb[kLB];        // left partial planes of chunks 1..X-1
+    int bad;              // set where a wave's planes hold a value that is not finite
 };
 
 template <>
@@ -132,6 +133,91 @@ __device__ __forceinline__ float4 ring4(const float (&v)[P + 1], int s) {
     return make_float4(c[0], c[1], c[2], c[3]);
 }
 
+// First position whose span, in the non-decreasing s[0..n), is at least t.
+__device__ __forceinline__ int first_at(const int *s, int n, int t) {
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (s[mid] < t) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// Component d of entry i of a table in LDS, read as one dword: a choice between
+// the components of the entry (pick4) is compiled to branches over addresses
+// where it stands in a divergent loop, and clang 22 forms the one of component 3
+// under the wrong execution mask there.
+__device__ __forceinline__ float entry(const float4 *tab, int i, int d) {
+    return reinterpret_cast<const float *>(tab)[4 * i + d];
+}
+
+// The planes [i0, i1) once more with every sum over its window alone, slice
+// by slice (slices [slo, shi) touch them): z into LDS, y and x by the thread
+// that owns (j, k).  The products of the matrix cores include zero weights,
+// so an infinite or NaN cotangent value turns whole tiles into NaN there;
+// here it reaches the p + 1 lattice indices of its window on each axis and no
+// others.  Only workgroups that found such a value come here.
+template <int P, bool DER>
+__device__ __forceinline__ void adj_windows(int ny, int nz, int ry, int rz, uint32_t mask,
+                                            const float *g, int64_t vox, float *Gb, int i0, int i1,
+                                            int slo, int shi, AmSmem<DER> &sm) {
+    constexpr int R = P + 1;
+    const int tid = threadIdx.x, plane = ny * nz;
+    float *z0 = sm.lb, *z1 = z0 + kAM * kAM, *z2 = z1 + kAM * kAM;
+    static_assert(3 * kAM * kAM <= kLB, "z sums of a slice");
+    // channels of the mask lie one after the other
+    const float *g0 = g, *g1 = g0 + (mask & 1u ? vox : 0), *g2 = g1 + (mask & 2u ? vox : 0),
+                *g3 = g2 + (mask & 4u ? vox : 0);
+    __syncthreads();
+    for (int e = tid; e < plane; e += kAT)
+        for (int i = i0; i < i1; ++i) Gb[(int64_t)i * plane + e] = 0.0f;
+    for (int u = slo; u < shi; ++u) {
+        __syncthreads();  // the previous slice's z sums are read
+        for (int e = tid; e < ry * nz; e += kAT) {
+            const int v = e / nz, k = e - v * nz;
+            const int64_t row = ((int64_t)u * ry + v) * rz;
+            float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
+            for (int w = first_at(sm.zs, rz, k); w < rz && sm.zs[w] <= k + P; ++w) {
+                const float n = entry(sm.zN, w, k - (sm.zs[w] - P));
+                if (mask & 1u) a0 = fmaf(n, g0[row + w], a0);
+                if constexpr (DER) {
+                    if (mask & 2u) a1 = fmaf(n, g1[row + w], a1);
+                    if (mask & 4u) a2 = fmaf(n, g2[row + w], a2);
+                    if (mask & 8u)
+                        a0 = fmaf(entry(sm.zD, w, k - (sm.zs[w] - P)), g3[row + w], a0);
+                }
+            }
+            z0[e] = a0;
+            if constexpr (DER) {
+                z1[e] = a1;
+                z2[e] = a2;
+            }
+        }
+        __syncthreads();
+        const int s = sm.xS[u];
+        for (int e = tid; e < plane; e += kAT) {
+            const int j = e / nz, k = e - j * nz;
+            float b0 = 0.0f, b1 = 0.0f;
+            for (int v = first_at(sm.ys, ry, j); v < ry && sm.ys[v] <= j + P; ++v) {
+                const int d = j - (sm.ys[v] - P);
+                const float n = entry(sm.yN, v, d);
+                b0 = fmaf(n, z0[v * nz + k], b0);
+                if constexpr (DER) {
+                    b0 = fmaf(entry(sm.yD, v, d), z2[v * nz + k], b0);
+                    b1 = fmaf(n, z1[v * nz + k], b1);
+                }
+            }
+            for (int i = max(s - P, i0); i <= min(s, i1 - 1); ++i) {
+                float *o = Gb + (int64_t)i * plane + e;
+                float sum = fmaf(entry(sm.xB, u, i % R), b0, *o);
+                if constexpr (DER) sum = fmaf(entry(sm.xD, u, i % R), b1, sum);
+                *o = sum;
+            }
+        }
+    }
+}
+
 // RAG: the rows of the cotangent are not whole 16-byte vectors (the values a
 // load takes from past its row's end are replaced by zeros)
 template <int P, bool DER, bool RAG>
@@ -152,6 +238,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         sm.tw[0][tid] = 0x7fffffff;
         sm.tw[1][tid] = -1;
     }
+    if (tid == 0) sm.bad = 0;
     lds_barrier();
     const float *tx = sm.kn, *ty = tx + nx + R, *tz = ty + ny + R;
     for (int t = tid; t < ry + rz; t += kAT) {
@@ -317,6 +404,10 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
     // buffer resource, the plane and row in the scalar offset.
     const __amdgpu_buffer_rsrc_t gs = make_rsrc(Gb, (uint32_t)((int64_t)nx * plane * 4));
     const int lane_e = 4 * gq * nz + k;
+    // NaN once a plane of this wave held a value that is not finite: such a
+    // value, or an overflow of the z product, is in every j of its tile column
+    // (the y product's zero weights turn it into NaN), so one j per lane shows it
+    float chk = 0.0f;
     const int lplane = open ? lbase : (c - 1) * R * plane;  // this chunk's planes in LDS
     auto put_plane = [&](int slot, float *dst, int i, const float *add)
         __attribute__((always_inline)) {
@@ -332,6 +423,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
 #pragma unroll
             for (int m = 0; m < R; ++m) {
                 if (m != slot) continue;
+                if (jj == 0) chk = fmaf(0.0f, ring[jj][m][0], chk);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int row = (16 * jt + r) * nz;  // uniform
@@ -593,8 +685,17 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         }
         // planes still in the ring that no chunk to the right shares
         for (int i = max(Lc, top - P); i <= top && (open || i < Lnext); ++i) flush(i);
+#pragma unroll
+        for (int m = 0; m < R; ++m) chk = fmaf(0.0f, ring[0][m][0], chk);  // those still shared
+        if (chk != chk) sm.bad = 1;
     }
     lds_barrier();  // left partial planes of every chunk in LDS
+    if (__builtin_amdgcn_readfirstlane(sm.bad)) {
+        const int64_t vox = (int64_t)rx * ry * rz;
+        adj_windows<P, DER>(ny, nz, ry, rz, mask, g + (int64_t)b * __builtin_popcount(mask) * vox,
+                            vox, Gb, i0, i1, slo, shi, sm);
+        return;
+    }
     if (open) {
         // every plane of the segment: the chunks that touch it, in order
         for (int e = tid; e < (i1 - i0) * plane; e += kAT) {
