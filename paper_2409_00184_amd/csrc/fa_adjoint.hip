@@ -71,6 +71,8 @@ constexpr int kAM = 64;          // res[1], res[2] and NCP_y, NCP_z limit
 constexpr int kJT = 2;           // j tiles per wave
 constexpr int kCUs = 256;
 constexpr int kMaxSegs = 8;      // segments of a micro-model
+// micro-models of one launch: a launch holds fewer than 2^32 threads
+constexpr int kMostGroups = 1 << 20;
 // partial planes of the chunk boundaries: at most (X - 1) (p + 1) NCP_y
 // NCP_z floats, X <= kAW / (k tiles x j tile pairs), which is below
 // (p + 1) * 4096 for every shape
@@ -750,9 +752,16 @@ hipError_t launch(const fa_block *blocks, int nblocks, const float *knots, int r
     if (attr != hipSuccess) return attr;
     // one workgroup fits a CU: segments while a CU would be without one
     const int nseg = std::max(1, std::min(kMaxSegs, kCUs / nblocks));
-    hipLaunchKernelGGL((adjoint_kernel<DER, RAG>), dim3((unsigned)nblocks * nseg), dim3(kAT),
-                       sizeof(AmSmem<DER>), s, blocks, nseg, knots, rx, ry, rz, mask, g, G);
-    return hipGetLastError();
+    const int64_t values = (int64_t)__builtin_popcount(mask) * rx * ry * rz;
+    for (int b0 = 0; b0 < nblocks; b0 += kMostGroups) {
+        const int n = std::min(nblocks - b0, kMostGroups);
+        hipLaunchKernelGGL((adjoint_kernel<DER, RAG>), dim3((unsigned)n * nseg), dim3(kAT),
+                           sizeof(AmSmem<DER>), s, blocks + b0, nseg, knots, rx, ry, rz, mask,
+                           g + b0 * values, G);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace
