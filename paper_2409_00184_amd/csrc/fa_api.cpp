@@ -24,6 +24,7 @@ namespace {
 
 constexpr int kDefaultRows = 8;
 constexpr int kItemsWanted = 1024;  // workgroups of a decode: four per CU
+constexpr int kItemVoxels = 8192;  // below, an item's set-up shows (tables, lattice slab)
 constexpr int kSearchPairs = 256;  // (block, candidate) pairs of an NCP search's launches
 
 struct Tune {
@@ -340,34 +341,52 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     const int nch = popcount4(ch);
     // Items are split along x where that pays (a segment's walk starts with
     // p + 1 control planes of its own):
-    // - a large batch of three or four channels is bound by its stores, and
-    //   segments of 16 positions, eight rows each, leave the chip storing to
-    //   fewer, denser regions at a time: 384 uneven blocks of 64^3 as records
-    //   260 us, whole walks 285 (four rows each: 291); planar, 512 blocks, 383
-    //   and 401 (444).  From eight
-    //   rounds of workgroups on (four of eight waves to a CU): 40 blocks of
-    //   96 x 80 x 48, two rounds, took 52 us split and 39 whole.
+    // - a large batch of all four channels is bound by its stores, and segments
+    //   of 16 positions, eight rows each, leave the chip storing to fewer,
+    //   denser regions at a time.  1024 blocks of 64^3 and degree 3, whole walks
+    //   1: records 0.89 at NCP 8, 0.91 at 18, 0.95 at 24, 1.00 at 32; planar
+    //   0.95, 0.97, 1.02, 1.05.  So a segment holds kItemVoxels at least (64 x
+    //   64 x 32 in 32 positions 0.98, in 16 1.12; 32^3 halved 1.25), and three
+    //   channels are not split (NCP 18: 1.22).  From eight rounds of workgroups
+    //   on (four of eight waves to a CU): 40 blocks of 96 x 80 x 48, two rounds,
+    //   took 52 us split and 39 whole.  With eight rounds of whole items, those
+    //   whose planes cost too much run whole (item_range; planar: from NCP 15 at
+    //   degree 3, 37 at degree 2); with fewer their tail costs more (384 blocks of
+    //   NCP 8..32: 300 us, all split 272).  Ordinary stores asked for on whole
+    //   lines are left in whole walks (4096 blocks, NCP 32, BF16: 3.67 ms, 3.21).
     // - few items leave CUs idle: down to eight positions a segment while
     //   there are fewer than four workgroups per CU (1 block: 24 -> 11 us).
     // A persistent grid (fewer workgroups than items) runs whole items.
-    const bool each = t.grid <= 0 || t.grid >= nblocks * items_per_block(res, t);
-    const bool dense = sep && each && nch >= 3 && t.rows >= 8 &&
-                       nblocks * items_per_block(res, t) * (res[0] / 16) >= 8 * kItemsWanted;
+    const int64_t items = nblocks * items_per_block(res, t);
+    const bool each = t.grid <= 0 || t.grid >= items;
+    // columns of an item: on average, but of the widest where two items share
+    // lines of the output (rows of 72, planar, 16 positions: 0.70; records 1.25)
+    const int ncolt = (res[2] + kWaveLanes - 1) / kWaveLanes;
+    const int cols = inter ? res[2] / ncolt : std::min(res[2], kWaveLanes);
+    const int slab_voxels = std::min(t.rows, res[1]) * cols;  // of an item, per x position
+    const int dense_segs = res[0] / std::max(16, (kItemVoxels + slab_voxels - 1) / slab_voxels);
+    const bool dense = sep && each && nch == 4 && t.rows >= 8 && t.store == 0 && dense_segs > 1 &&
+                       items * dense_segs >= 8 * kItemsWanted;
     // rows without a plan: four (512 uneven blocks, whole walks: 401 us, eight
-    // rows 408) but eight where a segment is short or there is one channel
+    // rows 408) but eight where a segment is short, where items of four rows
+    // would be small (32^3, NCP 16: 1.13) or there is one channel
     // (400 grids of 61 x 47 x 53: 79 us, four rows 91)
-    if (sep && free_rows && nch > 1 && !dense) {
+    const bool small = items >= kItemsWanted && 4 * cols * res[0] < kItemVoxels;
+    if (sep && free_rows && nch > 1 && !dense && !small) {
         t.rows = 4;
         if (!tune || tune->waves <= 0) t.waves = default_waves(t.rows);
     }
     DecodeLaunch a = grid_args(blocks, nblocks, knots, ctrl, dtype, res, ch, t, work, wg_off,
                                out);
     a.interleave = inter ? 1 : 0;
-    // - the matrix-core decode, two workgroups to a CU, gains from filling the
-    //   chip only (1 block: 65 -> 16 us; 128 blocks in halves 142 us, whole 119)
-    if (each) {
+    if (dense) {
+        a.xsegs = dense_segs;
+        if (items >= 8 * kItemsWanted) a.xcost = (inter ? 10 : 7) * res[0];
+    } else if (each) {
+        // (the matrix-core decode, two workgroups to a CU, gains from filling the
+        // chip only: 1 block 65 -> 16 us; 128 blocks in halves 142 us, whole 119)
         const int64_t fill = (sep ? kItemsWanted : kItemsWanted / 2) / a.nitems;
-        a.xsegs = dense ? res[0] / 16 : (int)std::max<int64_t>(1, std::min<int64_t>(fill, res[0] / 8));
+        a.xsegs = (int)std::max<int64_t>(1, std::min<int64_t>(fill, res[0] / 8));
     }
     if (work && (int64_t)ngroups * a.xsegs > kMostGroups) a.xsegs = 1;
     a.nitems *= a.xsegs;

@@ -40,6 +40,23 @@
 namespace fa {
 namespace {
 
+// The x positions [ua, ub) that segment seg of an item of micro-model B walks,
+// none if ua == ub.  A segment forms p + 1 control planes of its own before its
+// first position, (p + 1)^2 products a column each; where the planes of an
+// item's segments cost a.xcost or more, segment 0 walks the whole item and the
+// others do nothing.  Segments are then dealt to an item's workgroups from one
+// that a hash of the tile picks: always from the first, the working ones of
+// whole items would meet on a quarter of the CUs (1024 blocks of 64^3, NCP 32,
+// four workgroups an item: 1540 us; hashed 812; whole items from the outset 806).
+__device__ __forceinline__ void item_range(const DecodeLaunch &a, const fa_block &B, int64_t tile,
+                                           int seg, int &ua, int &ub) {
+    const int p = B.degree[0], segs = a.xsegs;
+    seg = (seg + (int)(((uint32_t)tile * 0x9e3779b1u) >> 16)) % segs;
+    const bool whole = (B.ncp[0] - p + segs * (p + 1)) * (p + 1) * (p + 1) >= a.xcost;
+    ua = whole ? 0 : seg * a.rx / segs;
+    ub = whole ? (seg == 0 ? a.rx : 0) : (seg + 1) * a.rx / segs;
+}
+
 template <int WAVES, bool NT, int MODE>
 __global__ __launch_bounds__(WAVES * 64) void decode_sep_kernel(DecodeLaunch a) {
     extern __shared__ float4 dyn_lds[];
@@ -61,6 +78,7 @@ __global__ __launch_bounds__(WAVES * 64) void decode_sep_kernel(DecodeLaunch a) 
     const int64_t per = (int64_t)a.nrowt * a.ncolt;
     for (int64_t it = beg; it < end; it += step) {
         int b, row0, nrows, col0;
+        int64_t tile = it;
         if (a.work) {
             const fa_work wk = a.work[it];
             b = wk.block;
@@ -70,15 +88,19 @@ __global__ __launch_bounds__(WAVES * 64) void decode_sep_kernel(DecodeLaunch a) 
         } else {
             // a tile's x segments in a row (a block's tiles of one segment in a
             // row: 270 us against 260 for 384 uneven blocks, records)
-            const int64_t t = it / a.xsegs;
-            seg = (int)(it - t * a.xsegs);
-            b = (int)(t / per);
-            const int r = (int)(t - (int64_t)b * per);
+            tile = it / a.xsegs;
+            seg = (int)(it - tile * a.xsegs);
+            b = (int)(tile / per);
+            const int r = (int)(tile - (int64_t)b * per);
             row0 = (r / a.ncolt) * a.rows;
             nrows = min(a.rows, a.ry - row0);
             col0 = (r % a.ncolt) * kWave;
         }
-        const int ua = seg * a.rx / a.xsegs, ub = (seg + 1) * a.rx / a.xsegs;
+        int ua = seg * a.rx / a.xsegs, ub = (seg + 1) * a.rx / a.xsegs;
+        if constexpr (MODE == 0 || MODE == 3) {  // (all four channels)
+            if (a.xcost != 0) item_range(a, a.blocks[b], tile, seg, ua, ub);
+            if (ua == ub) continue;  // uniform over the workgroup
+        }
         // the item's index in the default order, whatever order runs it
         const int64_t item = (int64_t)b * per + (row0 / a.rows) * a.ncolt + col0 / kWave;
         const int p = a.blocks[b].degree[0];

@@ -27,7 +27,8 @@ struct DecodeLaunch {
     const int32_t *wg_off;
     int rows;                // rows per item in default order
     int nrowt, ncolt;        // tiles per block (default order)
-    int xsegs;               // x segments per tile (default order)
+    int xsegs;               // x segments per tile, or per group of a plan
+    int xcost;               // items whose segments cost this much run whole; 0: no limit
     int64_t nitems;          // items in default order
     int slab;                // LDS slab floats
     int nt_store;            // 1: non-temporal stores
