@@ -109,8 +109,10 @@ typedef struct fa_tune {
                               the values are decoded)                           */
     int32_t waves;         /* waves (64 lanes) per workgroup: 1, 2, 4, 8
                               (default: one per row, up to 8)                   */
-    int32_t grid;          /* persistent workgroups (capped at the item count;
-                              default: one per item)                            */
+    int32_t grid;          /* most workgroups (capped at the item count; default:
+                              one per item).  fa_decode_blocks walks an item's x
+                              positions in several workgroups where that is
+                              faster and the grid holds them all               */
     int32_t kernel;        /* 0 = separable VALU, 1 = MFMA (BF16/FP16 lattices;
                               16 rows x 64 columns per item and 4 waves: pass
                               rows_per_item 0 or 16 and waves 0 or 4)       */

@@ -356,17 +356,19 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     //   lines are left in whole walks (4096 blocks, NCP 32, BF16: 3.67 ms, 3.21).
     // - few items leave CUs idle: down to eight positions a segment while
     //   there are fewer than four workgroups per CU (1 block: 24 -> 11 us).
-    // A persistent grid (fewer workgroups than items) runs whole items.
+    // A grid that the caller gives bounds the workgroups: items are split only as
+    // far as it holds one for every segment.
     const int64_t items = nblocks * items_per_block(res, t);
-    const bool each = t.grid <= 0 || t.grid >= items;
+    const int64_t most = t.grid > 0 ? std::min<int64_t>(t.grid, kMostGroups) : kMostGroups;
     // columns of an item: on average, but of the widest where two items share
     // lines of the output (rows of 72, planar, 16 positions: 0.70; records 1.25)
     const int ncolt = (res[2] + kWaveLanes - 1) / kWaveLanes;
     const int cols = inter ? res[2] / ncolt : std::min(res[2], kWaveLanes);
     const int slab_voxels = std::min(t.rows, res[1]) * cols;  // of an item, per x position
     const int dense_segs = res[0] / std::max(16, (kItemVoxels + slab_voxels - 1) / slab_voxels);
-    const bool dense = sep && each && nch == 4 && t.rows >= 8 && t.store == 0 && dense_segs > 1 &&
-                       items * dense_segs >= 8 * kItemsWanted;
+    const bool dense = sep && nch == 4 && t.rows >= 8 && t.store == 0 && dense_segs > 1 &&
+                       items * dense_segs >= 8 * kItemsWanted &&
+                       (t.grid <= 0 || items * dense_segs <= most);
     // rows without a plan: four (512 uneven blocks, whole walks: 401 us, eight
     // rows 408) but eight where a segment is short, where items of four rows
     // would be small (32^3, NCP 16: 1.13) or there is one channel
@@ -382,16 +384,16 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     if (dense) {
         a.xsegs = dense_segs;
         if (items >= 8 * kItemsWanted) a.xcost = (inter ? 10 : 7) * res[0];
-    } else if (each) {
+    } else if (t.grid <= 0 || t.grid >= a.nitems) {
         // (the matrix-core decode, two workgroups to a CU, gains from filling the
         // chip only: 1 block 65 -> 16 us; 128 blocks in halves 142 us, whole 119)
         const int64_t fill = (sep ? kItemsWanted : kItemsWanted / 2) / a.nitems;
         a.xsegs = (int)std::max<int64_t>(1, std::min<int64_t>(fill, res[0] / 8));
+        if (t.grid > 0) a.xsegs = (int)std::min<int64_t>(a.xsegs, t.grid / a.nitems);
     }
-    if (work && (int64_t)ngroups * a.xsegs > kMostGroups) a.xsegs = 1;
+    if (work && (int64_t)ngroups * a.xsegs > most) a.xsegs = 1;
     a.nitems *= a.xsegs;
-    const int grid = work ? ngroups * a.xsegs
-                          : (int)std::min<int64_t>(a.nitems, each ? kMostGroups : t.grid);
+    const int grid = work ? ngroups * a.xsegs : (int)std::min(a.nitems, most);
     hipError_t e;
     if (t.kernel == 1) e = launch_decode_mfma(a, t.waves, grid, (hipStream_t)stream);
     else e = launch_decode_sep(a, t.waves, grid, (hipStream_t)stream);
