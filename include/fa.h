@@ -106,7 +106,9 @@ typedef struct fa_work {
 typedef struct fa_tune {
     int32_t rows_per_item; /* y rows per work item, 1..64 (default 8; in
                               fa_decode_blocks without a plan 4 where more than
-                              the values are decoded)                           */
+                              one channel is decoded, unless eight waves are
+                              asked for, the batch is split along x or items of
+                              four rows would be small)                         */
     int32_t waves;         /* waves (64 lanes) per workgroup: 1, 2, 4, 8
                               (default: one per row, up to 8)                   */
     int32_t grid;          /* most workgroups (capped at the item count; default:

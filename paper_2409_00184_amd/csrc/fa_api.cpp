@@ -371,10 +371,11 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
                        (t.grid <= 0 || items * dense_segs <= most);
     // rows without a plan: four (512 uneven blocks, whole walks: 401 us, eight
     // rows 408) but eight where a segment is short, where items of four rows
-    // would be small (32^3, NCP 16: 1.13) or there is one channel
-    // (400 grids of 61 x 47 x 53: 79 us, four rows 91)
+    // would be small (32^3, NCP 16: 1.13), for eight waves that the caller asks for
+    // (500 grids of 64 x 64 x 40, two channels: 172 us, four rows 243) or one
+    // channel (400 grids of 61 x 47 x 53: 79 us, four rows 91)
     const bool small = items >= kItemsWanted && 4 * cols * res[0] < kItemVoxels;
-    if (sep && free_rows && nch > 1 && !dense && !small) {
+    if (sep && free_rows && nch > 1 && !dense && !small && !(tune && tune->waves > 4)) {
         t.rows = 4;
         if (!tune || tune->waves <= 0) t.waves = default_waves(t.rows);
     }

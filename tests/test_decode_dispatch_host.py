@@ -92,3 +92,19 @@ def test_given_grid_is_not_exceeded(launches, mask):
             assert r["nitems"] == _items(c["nblocks"], c["res"], r["rows"]) * r["xsegs"], (c, r)
         if grid < _items(c["nblocks"], c["res"], r["rows"]):
             assert r["xsegs"] == 1, (c, r)
+
+
+def test_rows_without_a_plan(launches):
+    """Rows left open: eight for one channel, for eight given waves, for a large
+    batch split along x and for one of small grids, else four; never more waves
+    than rows by default."""
+    cases = [(dict(nblocks=500, res=(64, 64, 40), mask=3, tune=[0, 8, 0, 0, 0, 0]), 8, 8),
+             (dict(nblocks=500, res=(64, 64, 40), mask=3, tune=[0, 4, 0, 0, 0, 0]), 4, 4),
+             (dict(nblocks=500, res=(64, 64, 40), mask=3, tune=[0, 0, 0, 0, 0, 0]), 4, 4),
+             (dict(nblocks=500, res=(64, 64, 40), mask=1, tune=[0, 0, 0, 0, 0, 0]), 8, 8),
+             (dict(nblocks=512, res=(64, 64, 64), mask=15, tune=[0, 0, 0, 0, 0, 0]), 8, 8),
+             (dict(nblocks=512, res=(64, 64, 64), mask=14, tune=[0, 0, 0, 0, 0, 0]), 4, 4),
+             (dict(nblocks=8192, res=(32, 32, 32), mask=15, tune=[0, 0, 0, 0, 0, 0]), 8, 8),
+             (dict(nblocks=8, res=(32, 32, 32), mask=15, tune=[0, 0, 0, 0, 0, 0]), 4, 4)]
+    for (c, rows, waves), r in zip(cases, launches([c for c, _, _ in cases])):
+        assert (r["status"], r["rows"], r["waves"]) == (0, rows, waves), (c, r)
