@@ -120,10 +120,11 @@ typedef struct fa_tune {
                               rows_per_item 0 or 16 and waves 0 or 4)       */
     int32_t slab_floats;   /* LDS lattice slab, 4096..16384 floats (default 8192);
                               larger lattices are staged in x chunks            */
-    int32_t store;         /* 0 = non-temporal stores where a z row is whole
-                              128-byte lines, 1 = ordinary stores (separable
-                              VALU kernel; the MFMA kernel always stores
-                              ordinarily)                                    */
+    int32_t store;         /* 0 = non-temporal stores where they are faster (z
+                              rows of whole 128-byte lines; narrow planar rows
+                              of whole 16 bytes; records, an even number a row),
+                              1 = ordinary stores (separable VALU kernel; the
+                              MFMA kernel always stores ordinarily)          */
 } fa_tune;
 
 const char *fa_status_string(fa_status s);

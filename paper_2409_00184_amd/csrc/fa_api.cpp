@@ -382,6 +382,14 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     DecodeLaunch a = grid_args(blocks, nblocks, knots, ctrl, dtype, res, ch, t, work, wg_off,
                                out);
     a.interleave = inter ? 1 : 0;
+    // Non-temporal stores also for records of an even number a row (32-byte
+    // pieces; over NCP 8, 8..32 and 24, ordinary stores 1: 0.76-0.78 at rows of
+    // 12, 0.69-1.04 at 16, 0.77-1.04 at 24, 0.81-1.0 at 36, 0.95-1.2 at 48,
+    // 0.86-1.06 at 60; 1.2 at 53) and for narrow planar rows of whole 16-byte
+    // pieces, whose items are whole lines (0.79-0.86 at 12, 0.74-0.89 at 16,
+    // 0.80-1.05 at 24, 0.87-1.0 at 28; 0.82-1.07 at 36, 1.0-1.2 at 48, 60 and
+    // 1.3-1.6 at 62 are left)
+    if (t.store == 0 && (inter ? res[2] % 2 == 0 : res[2] <= 32 && res[2] % 4 == 0)) a.nt_store = 1;
     if (dense) {
         a.xsegs = dense_segs;
         if (items >= 8 * kItemsWanted) a.xcost = (inter ? 10 : 7) * res[0];

@@ -108,3 +108,17 @@ def test_rows_without_a_plan(launches):
              (dict(nblocks=8, res=(32, 32, 32), mask=15, tune=[0, 0, 0, 0, 0, 0]), 4, 4)]
     for (c, rows, waves), r in zip(cases, launches([c for c, _, _ in cases])):
         assert (r["status"], r["rows"], r["waves"]) == (0, rows, waves), (c, r)
+
+
+def test_store_kind(launches):
+    """store = 0: non-temporal by the bytes of a row of the layout that is
+    written, a record's being four times a planar row's; store = 1: ordinary."""
+    wanted = {15: {64, 96, 32, 16, 12, 4, 28}, 1: {64, 96, 32, 16, 12, 4, 28},
+              15 | 0x100: {64, 96, 32, 16, 12, 4, 28, 36, 40, 48, 72, 62, 18}}
+    cases = [dict(nblocks=100, res=(64, 64, rz), mask=mask, tune=[0, 0, 0, 0, 0, store])
+             for mask in wanted for store in (0, 1)
+             for rz in (4, 12, 13, 16, 18, 28, 32, 36, 40, 48, 53, 62, 64, 72, 96)]
+    for c, r in zip(cases, launches(cases)):
+        rz, store = c["res"][2], c["tune"][5]
+        nt = store == 0 and rz in wanted[c["mask"]]
+        assert r["nt_store"] == int(nt), (c, r)
