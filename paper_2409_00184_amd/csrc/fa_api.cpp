@@ -352,8 +352,11 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     //   took 52 us split and 39 whole.  With eight rounds of whole items, those
     //   whose planes cost too much run whole (item_range; planar: from NCP 15 at
     //   degree 3, 37 at degree 2); with fewer their tail costs more (384 blocks of
-    //   NCP 8..32: 300 us, all split 272).  Ordinary stores asked for on whole
-    //   lines are left in whole walks (4096 blocks, NCP 32, BF16: 3.67 ms, 3.21).
+    //   NCP 8..32: 300 us, all split 272), and lines that two items share gain
+    //   from the split whatever the planes cost (600 blocks of 64 x 64 x 72, NCP
+    //   32, planar: 0.99 ms, all split 0.92; 2000 of 48^3, lines of one item, 0.91
+    //   and 0.98).  Ordinary stores asked for are left in whole walks (4096
+    //   blocks, NCP 32, BF16: 3.67 ms split, 3.21).
     // - few items leave CUs idle: down to eight positions a segment while
     //   there are fewer than four workgroups per CU (1 block: 24 -> 11 us).
     // A grid that the caller gives bounds the workgroups: items are split only as
@@ -367,14 +370,18 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     const int slab_voxels = std::min(t.rows, res[1]) * cols;  // of an item, per x position
     const int dense_segs = res[0] / std::max(16, (kItemVoxels + slab_voxels - 1) / slab_voxels);
     const bool dense = sep && nch == 4 && t.rows >= 8 && t.store == 0 && dense_segs > 1 &&
-                       items * dense_segs >= 8 * kItemsWanted &&
+                       items * (res[0] / 16) >= 8 * kItemsWanted &&
                        (t.grid <= 0 || items * dense_segs <= most);
     // rows without a plan: four (512 uneven blocks, whole walks: 401 us, eight
     // rows 408) but eight where a segment is short, where items of four rows
-    // would be small (32^3, NCP 16: 1.13), for eight waves that the caller asks for
+    // would be small (32^3, NCP 16: 1.13), for three channels of narrow rows
+    // (1024 blocks of 64 x 64 x 48, NCP 32: 590 us, four rows 659; where rows are
+    // not whole 16 bytes 1.1-1.3 times), for eight waves that the caller asks for
     // (500 grids of 64 x 64 x 40, two channels: 172 us, four rows 243) or one
     // channel (400 grids of 61 x 47 x 53: 79 us, four rows 91)
-    const bool small = items >= kItemsWanted && 4 * cols * res[0] < kItemVoxels;
+    const bool small = items >= 2 * kItemsWanted &&
+                       (4 * cols * res[0] < kItemVoxels ||
+                        (nch == 3 && res[2] <= 56 && res[2] % 4 == 0));
     if (sep && free_rows && nch > 1 && !dense && !small && !(tune && tune->waves > 4)) {
         t.rows = 4;
         if (!tune || tune->waves <= 0) t.waves = default_waves(t.rows);
@@ -392,7 +399,8 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     if (t.store == 0 && (inter ? res[2] % 2 == 0 : res[2] <= 32 && res[2] % 4 == 0)) a.nt_store = 1;
     if (dense) {
         a.xsegs = dense_segs;
-        if (items >= 8 * kItemsWanted) a.xcost = (inter ? 10 : 7) * res[0];
+        if (items >= 8 * kItemsWanted && (a.nt_store || ncolt == 1))
+            a.xcost = (inter ? 10 : 7) * res[0];
     } else if (t.grid <= 0 || t.grid >= a.nitems) {
         // (the matrix-core decode, two workgroups to a CU, gains from filling the
         // chip only: 1 block 65 -> 16 us; 128 blocks in halves 142 us, whole 119)

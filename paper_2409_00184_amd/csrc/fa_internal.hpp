@@ -28,7 +28,6 @@ struct DecodeLaunch {
     int rows;                // rows per item in default order
     int nrowt, ncolt;        // tiles per block (default order)
     int xsegs;               // x segments per tile, or per group of a plan
-    int xcost;               // items whose segments cost this much run whole; 0: no limit
     int64_t nitems;          // items in default order
     int slab;                // LDS slab floats
     int nt_store;            // 1: non-temporal stores
@@ -45,6 +44,8 @@ struct DecodeLaunch {
     // decode form: all four channels stored as one 16-byte record per voxel,
     // out = [block][u][v][w][4]
     int interleave;
+    // items whose x segments cost this much run whole; 0: no limit
+    int xcost;
 };
 
 hipError_t launch_decode_sep(const DecodeLaunch &a, int waves, int grid, hipStream_t s);
