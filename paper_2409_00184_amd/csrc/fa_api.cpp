@@ -359,8 +359,8 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
     //   blocks, NCP 32, BF16: 3.67 ms split, 3.21).
     // - few items leave CUs idle: down to eight positions a segment while
     //   there are fewer than four workgroups per CU (1 block: 24 -> 11 us).
-    // A grid that the caller gives bounds the workgroups: items are split only as
-    // far as it holds one for every segment.
+    // A grid that the caller gives bounds the workgroups, kMostGroups any other:
+    // items are split only where there can be one for every segment.
     const int64_t items = nblocks * items_per_block(res, t);
     const int64_t most = t.grid > 0 ? std::min<int64_t>(t.grid, kMostGroups) : kMostGroups;
     // columns of an item: on average, but of the widest where two items share
@@ -408,7 +408,7 @@ fa_status fa_decode_blocks(const fa_block *blocks, int32_t nblocks, const float 
         a.xsegs = (int)std::max<int64_t>(1, std::min<int64_t>(fill, res[0] / 8));
         if (t.grid > 0) a.xsegs = (int)std::min<int64_t>(a.xsegs, t.grid / a.nitems);
     }
-    if (work && (int64_t)ngroups * a.xsegs > most) a.xsegs = 1;
+    if ((work ? ngroups : a.nitems) * a.xsegs > most) a.xsegs = 1;
     a.nitems *= a.xsegs;
     const int grid = work ? ngroups * a.xsegs : (int)std::min(a.nitems, most);
     hipError_t e;

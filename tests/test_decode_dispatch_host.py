@@ -122,3 +122,15 @@ def test_store_kind(launches):
         rz, store = c["res"][2], c["tune"][5]
         nt = store == 0 and rz in wanted[c["mask"]]
         assert r["nt_store"] == int(nt), (c, r)
+
+
+def test_more_segments_than_a_launch_holds(launches):
+    """Batches whose segments come to more than 2^20 workgroups run whole items,
+    several to a workgroup above 2^20 items."""
+    cases = [dict(nblocks=n, res=res, mask=15, tune=[0] * 6, groups=groups)
+             for n, res, groups in ((40000, (64, 64, 64), 0), (40000, (64, 64, 64), 320000),
+                                    (30000, (64, 64, 64), 0), (2 << 20, (8, 8, 8), 0))]
+    r = launches(cases)
+    assert [x["status"] for x in r] == [0] * 4
+    assert [(x["xsegs"], x["grid"]) for x in r] == [(1, 320000), (1, 320000), (4, 960000), (1, 1 << 20)]
+    assert r[3]["nitems"] == 2 << 20
