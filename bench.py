@@ -300,6 +300,8 @@ def bench_c2(args):
     pers = []
     t = plan.tune
     for grid in (512, 768, 1024, 1536, 2048):
+        if grid >= plan.nwork:  # one workgroup per item: not persistent
+            continue
         pp = fa.Plan(m, res, t.rows_per_item, t.waves, grid, 0, t.slab_floats, t.store)
         o3 = torch.empty((batch.nblocks,) + res + (4,), dtype=torch.float32, device="cuda")
         g3, _ = fa.capture(lambda: fa.decode(m, res, mask, plan=pp, out=o3))
