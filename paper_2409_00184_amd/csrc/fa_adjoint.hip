@@ -92,7 +92,7 @@ struct AmSmem<false> {
     int zs[kAM];
     int tw[2][kAM / 16];  // first and last w with a basis entry in each k tile
     float lb[kLB];        // left partial planes of chunks 1..X-1
-    int bad;              // set where a wave's planes hold a value that is not finite
+    uint32_t bad[kAM / 32];  // planes in which a wave holds a value that is not finite
 };
 
 template <>
@@ -101,7 +101,7 @@ struct AmSmem<true> : AmSmem<false> {
     // operands in lane order, basis then derivative: the z product's of k
     // tile t and columns 16q + 4(l/16) + (x, y, z, w), the y product's of j
     // tile t and rows 16m + 4(l/16) + (x, y, z, w)
-    float4 zop[2][kAM / 16][4][kWave], yop[2][kAM / 16][4][kWave];
+    float4 op[2][2][kAM / 16][4][kWave];  // z product, y product
 };
 
 __device__ __forceinline__ f32x4a mma4(float a, float b, const f32x4a &c) {
@@ -154,40 +154,65 @@ __device__ __forceinline__ float entry(const float4 *tab, int i, int d) {
     return reinterpret_cast<const float *>(tab)[4 * i + d];
 }
 
-// The planes [i0, i1) once more with every sum over its window alone, slice
-// by slice (slices [slo, shi) touch them): z into LDS, y and x by the thread
-// that owns (j, k).  The products of the matrix cores include zero weights,
-// so an infinite or NaN cotangent value turns whole tiles into NaN there;
-// here it reaches the p + 1 lattice indices of its window on each axis and no
-// others.  Only workgroups that found such a value come here.
+// The planes of the set `bad` once more with every sum over its window alone,
+// by the slices of [slo, shi) that touch them: a slice's channels into LDS, their
+// z sums into LDS, y and x by the thread that owns (j, k).  The products of the
+// matrix cores include zero weights, so an infinite or NaN cotangent value turns
+// whole tiles into NaN there; here it reaches the p + 1 lattice indices of its
+// window on each axis and no others.  Only workgroups that found such a value
+// come here, for the planes that hold one.  Bound by the latency of its sums'
+// LDS reads: 128 blocks of 64^3, all channels, one NaN in each, 0.55 ms at NCP 32,
+// 1.4 at 8..32, 2.0 at 4 (finite 0.15, 0.20, 0.19).
 template <int P, bool DER>
 __device__ __forceinline__ void adj_windows(int ny, int nz, int ry, int rz, uint32_t mask,
-                                            const float *g, int64_t vox, float *Gb, int i0, int i1,
+                                            const float *g, int64_t vox, float *Gb, uint64_t bad,
                                             int slo, int shi, AmSmem<DER> &sm) {
-    constexpr int R = P + 1;
-    const int tid = threadIdx.x, plane = ny * nz;
-    float *z0 = sm.lb, *z1 = z0 + kAM * kAM, *z2 = z1 + kAM * kAM;
-    static_assert(3 * kAM * kAM <= kLB, "z sums of a slice");
-    // channels of the mask lie one after the other
-    const float *g0 = g, *g1 = g0 + (mask & 1u ? vox : 0), *g2 = g1 + (mask & 2u ? vox : 0),
-                *g3 = g2 + (mask & 4u ? vox : 0);
+    constexpr int R = P + 1, kS = kAM * kAM;
+    const int tid = threadIdx.x, plane = ny * nz, row = ry * rz;
+    float *z0 = sm.lb, *z1 = z0 + kS, *z2 = z1 + kS;  // z sums of a slice
+    // channel c of the slice at c kS, row v turned by v (rows in step would meet
+    // on one bank)
+    float *gl;
+    if constexpr (DER) gl = reinterpret_cast<float *>(sm.op);
+    else gl = z1;
+    static_assert(3 * kS <= kLB, "z sums of a slice");
     __syncthreads();
     for (int e = tid; e < plane; e += kAT)
-        for (int i = i0; i < i1; ++i) Gb[(int64_t)i * plane + e] = 0.0f;
+        for (uint64_t m = bad; m; m &= m - 1)
+            Gb[(int64_t)__builtin_ctzll(m) * plane + e] = 0.0f;
     for (int u = slo; u < shi; ++u) {
+        const int s = __builtin_amdgcn_readfirstlane(sm.xS[u]);
+        const uint32_t hit = (uint32_t)(bad >> (s - P)) & ((1u << R) - 1u);  // of its planes
+        if (!hit) continue;
         __syncthreads();  // the previous slice's z sums are read
+        const float *src = g + (int64_t)u * row;
+        for (int c = 0; c < (DER ? 4 : 1); ++c) {
+            const bool has = mask >> c & 1u;
+#pragma unroll
+            for (int q = 0; q < kS / kAT; ++q) {
+                const int e = tid + q * kAT, v = e / rz, t = e - v * rz + v % rz;
+                if (e < row) gl[c * kS + v * rz + (t < rz ? t : t - rz)] = has ? src[e] : 0.0f;
+            }
+            src += has ? vox : 0;
+        }
+        __syncthreads();
         for (int e = tid; e < ry * nz; e += kAT) {
             const int v = e / nz, k = e - v * nz;
-            const int64_t row = ((int64_t)u * ry + v) * rz;
+            const float *gv = gl + v * rz;
+            const int turn = v % rz;
             float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
-            for (int w = first_at(sm.zs, rz, k); w < rz && sm.zs[w] <= k + P; ++w) {
-                const float n = entry(sm.zN, w, k - (sm.zs[w] - P));
-                if (mask & 1u) a0 = fmaf(n, g0[row + w], a0);
+            // (a channel that is not there was staged as zeros)
+            const int wb = first_at(sm.zs, rz, k), we = first_at(sm.zs, rz, k + P + 1);
+#pragma unroll 4
+            for (int w = wb; w < we; ++w) {
+                const int d = k - (sm.zs[w] - P);
+                const float n = entry(sm.zN, w, d);
+                const int t = w + turn < rz ? w + turn : w + turn - rz;
+                a0 = fmaf(n, gv[t], a0);
                 if constexpr (DER) {
-                    if (mask & 2u) a1 = fmaf(n, g1[row + w], a1);
-                    if (mask & 4u) a2 = fmaf(n, g2[row + w], a2);
-                    if (mask & 8u)
-                        a0 = fmaf(entry(sm.zD, w, k - (sm.zs[w] - P)), g3[row + w], a0);
+                    a1 = fmaf(n, gv[kS + t], a1);
+                    a2 = fmaf(n, gv[2 * kS + t], a2);
+                    a0 = fmaf(entry(sm.zD, w, d), gv[3 * kS + t], a0);
                 }
             }
             z0[e] = a0;
@@ -197,11 +222,12 @@ __device__ __forceinline__ void adj_windows(int ny, int nz, int ry, int rz, uint
             }
         }
         __syncthreads();
-        const int s = sm.xS[u];
         for (int e = tid; e < plane; e += kAT) {
             const int j = e / nz, k = e - j * nz;
             float b0 = 0.0f, b1 = 0.0f;
-            for (int v = first_at(sm.ys, ry, j); v < ry && sm.ys[v] <= j + P; ++v) {
+            const int vb = first_at(sm.ys, ry, j), ve = first_at(sm.ys, ry, j + P + 1);
+#pragma unroll 4
+            for (int v = vb; v < ve; ++v) {
                 const int d = j - (sm.ys[v] - P);
                 const float n = entry(sm.yN, v, d);
                 b0 = fmaf(n, z0[v * nz + k], b0);
@@ -210,11 +236,16 @@ __device__ __forceinline__ void adj_windows(int ny, int nz, int ry, int rz, uint
                     b1 = fmaf(n, z1[v * nz + k], b1);
                 }
             }
-            for (int i = max(s - P, i0); i <= min(s, i1 - 1); ++i) {
-                float *o = Gb + (int64_t)i * plane + e;
-                float sum = fmaf(entry(sm.xB, u, i % R), b0, *o);
-                if constexpr (DER) sum = fmaf(entry(sm.xD, u, i % R), b1, sum);
-                *o = sum;
+            float *o = Gb + (int64_t)(s - P) * plane + e, sum[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r)  // all loads, then the stores
+                sum[r] = hit >> r & 1u ? o[(int64_t)r * plane] : 0.0f;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int slot = (s - P + r) % R;
+                sum[r] = fmaf(entry(sm.xB, u, slot), b0, sum[r]);
+                if constexpr (DER) sum[r] = fmaf(entry(sm.xD, u, slot), b1, sum[r]);
+                if (hit >> r & 1u) o[(int64_t)r * plane] = sum[r];
             }
         }
     }
@@ -240,7 +271,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         sm.tw[0][tid] = 0x7fffffff;
         sm.tw[1][tid] = -1;
     }
-    if (tid == 0) sm.bad = 0;
+    if (tid < kAM / 32) sm.bad[tid] = 0u;
     lds_barrier();
     const float *tx = sm.kn, *ty = tx + nx + R, *tz = ty + ny + R;
     for (int t = tid; t < ry + rz; t += kAT) {
@@ -297,7 +328,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
 #pragma unroll
                 for (int r = 0; r < 4; ++r) f[r] = zval(p0 + r, i, d ? sm.zD : sm.zN);
             }
-            (e >> 11 ? sm.yop : sm.zop)[d][t][q][l] = make_float4(f[0], f[1], f[2], f[3]);
+            sm.op[e >> 11][d][t][q][l] = make_float4(f[0], f[1], f[2], f[3]);
         }
         lds_barrier();
     }
@@ -406,10 +437,12 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
     // buffer resource, the plane and row in the scalar offset.
     const __amdgpu_buffer_rsrc_t gs = make_rsrc(Gb, (uint32_t)((int64_t)nx * plane * 4));
     const int lane_e = 4 * gq * nz + k;
-    // NaN once a plane of this wave held a value that is not finite: such a
-    // value, or an overflow of the z product, is in every j of its tile column
-    // (the y product's zero weights turn it into NaN), so one j per lane shows it
-    float chk = 0.0f;
+    // marks plane i if one of its values v is not finite: such a value, or an
+    // overflow of the z product, is in every j of its tile column (the y product's
+    // zero weights turn it into NaN), so one j per lane shows it
+    auto mark = [&](int i, float v) __attribute__((always_inline)) {
+        if (!(fabsf(v) <= 3.402823466e38f)) atomicOr(&sm.bad[i >> 5], 1u << (i & 31));
+    };
     const int lplane = open ? lbase : (c - 1) * R * plane;  // this chunk's planes in LDS
     auto put_plane = [&](int slot, float *dst, int i, const float *add)
         __attribute__((always_inline)) {
@@ -425,7 +458,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
 #pragma unroll
             for (int m = 0; m < R; ++m) {
                 if (m != slot) continue;
-                if (jj == 0) chk = fmaf(0.0f, ring[jj][m][0], chk);
+                if (jj == 0) mark(i, ring[jj][m][0]);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int row = (16 * jt + r) * nz;  // uniform
@@ -604,7 +637,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                 auto zmul = [&](const float4(&f)[4][NQ], int d) __attribute__((always_inline)) {
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
-                        const float4 o = sm.zop[d][nt][min(q0 + q, 3)][ln];
+                        const float4 o = sm.op[0][d][nt][min(q0 + q, 3)][ln];
                         const float ov[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
@@ -620,7 +653,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
                         for (int jj = 0; jj < NJ; ++jj) {
-                            const float4 o = sm.yop[d][2 * jp + jj][mt][ln];
+                            const float4 o = sm.op[1][d][2 * jp + jj][mt][ln];
                             Y[jj] = mma4(o.x, Z[mt][0], Y[jj]);
                             Yo[jj] = mma4(o.y, Z[mt][1], Yo[jj]);
                             Y[jj] = mma4(o.z, Z[mt][2], Y[jj]);
@@ -688,16 +721,15 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         // planes still in the ring that no chunk to the right shares
         for (int i = max(Lc, top - P); i <= top && (open || i < Lnext); ++i) flush(i);
 #pragma unroll
-        for (int m = 0; m < R; ++m) chk = fmaf(0.0f, ring[0][m][0], chk);  // those still shared
-        if (chk != chk) sm.bad = 1;
+        for (int m = 0; m < R; ++m)  // and those that it does: plane top - (top - m) mod R
+            mark(max(top - (top - m + R) % R, 0), ring[0][m][0]);
     }
     lds_barrier();  // left partial planes of every chunk in LDS
-    if (__builtin_amdgcn_readfirstlane(sm.bad)) {
-        const int64_t vox = (int64_t)rx * ry * rz;
-        adj_windows<P, DER>(ny, nz, ry, rz, mask, g + (int64_t)b * __builtin_popcount(mask) * vox,
-                            vox, Gb, i0, i1, slo, shi, sm);
-        return;
-    }
+    uint64_t bad = 0;
+#pragma unroll
+    for (int w = 0; w < kAM / 32; ++w)
+        bad |= (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)sm.bad[w]) << (32 * w);
+    bad &= (~0ull >> (64 - i1)) & (~0ull << i0);  // of this segment
     if (open) {
         // every plane of the segment: the chunks that touch it, in order
         for (int e = tid; e < (i1 - i0) * plane; e += kAT) {
@@ -712,9 +744,8 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
             }
             Gb[(int64_t)i * plane + r] = sum;
         }
-        return;
     }
-    if (active && c + 1 < X) {
+    if (!open && active && c + 1 < X) {
         // planes shared with the chunk to the right: its partial + this one
         for (int i = Lnext; i <= top; ++i)
             put_plane(i % R, nullptr, i, sm.lb + (c * R + (i - Lnext)) * plane);
@@ -723,8 +754,15 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
     // and after its last one's
     const int lo = __builtin_amdgcn_readfirstlane(sm.xS[slo]) - P;
     const int hl = max(__builtin_amdgcn_readfirstlane(sm.xS[shi - 1]) + 1, i0);
-    for (int e = tid; e < (min(lo, i1) - i0) * plane; e += kAT) Gb[(int64_t)i0 * plane + e] = 0.0f;
-    for (int e = tid; e < (i1 - hl) * plane; e += kAT) Gb[(int64_t)hl * plane + e] = 0.0f;
+    if (!open) {
+        for (int e = tid; e < (min(lo, i1) - i0) * plane; e += kAT) Gb[(int64_t)i0 * plane + e] = 0.0f;
+        for (int e = tid; e < (i1 - hl) * plane; e += kAT) Gb[(int64_t)hl * plane + e] = 0.0f;
+    }
+    if (bad) {
+        const int64_t vox = (int64_t)rx * ry * rz;
+        adj_windows<P, DER>(ny, nz, ry, rz, mask, g + (int64_t)b * __builtin_popcount(mask) * vox,
+                            vox, Gb, bad, slo, shi, sm);
+    }
 }
 
 template <bool DER, bool RAG>
