@@ -275,8 +275,8 @@ def bench_c2(args):
                                "{8,12,16,24,32}, degree in {2,3}, 64^3 voxels each, value + 3 "
                                "gradients, FP32, one launch over the batch plan's work items "
                                "in longest-first order at the autotuner's schedule (one "
-                               "workgroup per item), replayed from a HIP graph, one 16-byte "
-                               "record per voxel",
+                               "workgroup per item or x segment of one), replayed from a HIP "
+                               "graph, one 16-byte record per voxel",
                    "nblocks": batch.nblocks, "res": list(res), "channels": 4,
                    "layout": "[block][x][y][z][value, d/du, d/dv, d/dw]",
                    "schedule": {"rows_per_item": plan.tune.rows_per_item,

@@ -37,7 +37,7 @@ struct DecodeLaunch {
     const float *samples;    // null: plain decode
     float gscale;
     double *partials;
-    // error form (samples set, errs set, nothing stored per voxel): per-item
+    // error form (samples and error_form set, nothing stored per voxel): per-item
     // max |f - samples| and FP64 sum of squares into partials[2 item + {0,1}]
     int error_form;
     int nsrc;                // entry e reads the samples of block e % nsrc
