@@ -92,7 +92,7 @@ struct AmSmem<false> {
     int zs[kAM];
     int tw[2][kAM / 16];  // first and last w with a basis entry in each k tile
     float lb[kLB];        // left partial planes of chunks 1..X-1
-    uint32_t bad[kAM / 32];  // planes in which a wave holds a value that is not finite
+    uint32_t bad[2];      // planes in which a wave holds a value that is not finite
 };
 
 template <>
@@ -160,9 +160,9 @@ __device__ __forceinline__ float entry(const float4 *tab, int i, int d) {
 // matrix cores include zero weights, so an infinite or NaN cotangent value turns
 // whole tiles into NaN there; here it reaches the p + 1 lattice indices of its
 // window on each axis and no others.  Only workgroups that found such a value
-// come here, for the planes that hold one.  Bound by the latency of its sums'
-// LDS reads: 128 blocks of 64^3, all channels, one NaN in each, 0.55 ms at NCP 32,
-// 1.4 at 8..32, 2.0 at 4 (finite 0.15, 0.20, 0.19).
+// come here, for the marked planes.  Bound by the latency of its sums' LDS reads:
+// 128 blocks of 64^3, all channels, one NaN in each, 0.55 ms at NCP 32, 1.4 at
+// 8..32, 1.9 at 4 (finite 0.15, 0.20, 0.18).
 template <int P, bool DER>
 __device__ __forceinline__ void adj_windows(int ny, int nz, int ry, int rz, uint32_t mask,
                                             const float *g, int64_t vox, float *Gb, uint64_t bad,
@@ -271,7 +271,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         sm.tw[0][tid] = 0x7fffffff;
         sm.tw[1][tid] = -1;
     }
-    if (tid < kAM / 32) sm.bad[tid] = 0u;
+    if (tid < 2) sm.bad[tid] = 0u;
     lds_barrier();
     const float *tx = sm.kn, *ty = tx + nx + R, *tz = ty + ny + R;
     for (int t = tid; t < ry + rz; t += kAT) {
@@ -352,6 +352,8 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const int u = 64 * w + lane;
+        first[w] = 0;
+        if (64 * w >= rx) continue;  // uniform
         first[w] = __ballot(u < rx && u > 0 && sm.xS[u] != sm.xS[u - 1]);
         slo += __builtin_popcountll(__ballot(u < rx && sm.xS[u] < i0));
         shi += __builtin_popcountll(__ballot(u < rx && sm.xS[u] - P < i1));
@@ -395,11 +397,13 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
     // planes it touches fits in LDS; each chunk leaves all of its planes there
     // and the sums over the chunks follow the barrier (128 blocks of 8^3, all
     // channels: 211 -> 151 us).  At half the waves idle the copies cost more
-    // than they give (128 blocks of 16..32, values: 51 us without, 59 with).
+    // than they give (128 blocks of 16..32, values: 51 us without, 59 with), and
+    // so they do for the values in chunks of fewer than three slices (50000 blocks
+    // of 8^3 on 8^3: 2.70 ms without, 3.19 with; all channels 5.09, 4.12).
     const int XO = min(kAW / W1, len);
     int lbase = 0;
     bool open = false;
-    if (3 * X <= XO) {
+    if (3 * X <= XO && (DER || len >= 3 * XO)) {
         int total = 0;
         for (int c = 0; c < XO; ++c) {
             if (c == cw) lbase = total;
@@ -437,11 +441,22 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
     // buffer resource, the plane and row in the scalar offset.
     const __amdgpu_buffer_rsrc_t gs = make_rsrc(Gb, (uint32_t)((int64_t)nx * plane * 4));
     const int lane_e = 4 * gq * nz + k;
-    // marks plane i if one of its values v is not finite: such a value, or an
-    // overflow of the z product, is in every j of its tile column (the y product's
-    // zero weights turn it into NaN), so one j per lane shows it
-    auto mark = [&](int i, float v) __attribute__((always_inline)) {
-        if (!(fabsf(v) <= 3.402823466e38f)) atomicOr(&sm.bad[i >> 5], 1u << (i & 31));
+    // the planes that hold a value which is not finite are marked: such a value,
+    // or an overflow of the z product, is in every j of its tile column (the y
+    // product's zero weights turn it into NaN), so one j per lane shows it.  With
+    // derivatives plane by plane as they leave the ring; for the values by a sum
+    // that turns NaN and stands for all of the chunk's planes, cheaper where chunks
+    // are short (50000 blocks of 8^3: 2.82 ms, 2.86 plane by plane; 256 of 64^3:
+    // 97 us either way).  All channels of 128 blocks of 64^3: 267 us either way, but
+    // with NaN in the data the planes of the sum take 0.76 ms, single planes 0.55
+    float chk = 0.0f;
+    auto mark = [&](uint64_t set) __attribute__((always_inline)) {
+        if ((uint32_t)set) atomicOr(&sm.bad[0], (uint32_t)set);
+        if ((uint32_t)(set >> 32)) atomicOr(&sm.bad[1], (uint32_t)(set >> 32));
+    };
+    auto check = [&](float v, int i) __attribute__((always_inline)) {
+        if constexpr (!DER) chk = fmaf(0.0f, v, chk);
+        else if (!(fabsf(v) <= 3.402823466e38f)) atomicOr(&sm.bad[i >> 5], 1u << (i & 31));
     };
     const int lplane = open ? lbase : (c - 1) * R * plane;  // this chunk's planes in LDS
     auto put_plane = [&](int slot, float *dst, int i, const float *add)
@@ -458,7 +473,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
 #pragma unroll
             for (int m = 0; m < R; ++m) {
                 if (m != slot) continue;
-                if (jj == 0) mark(i, ring[jj][m][0]);
+                if (jj == 0) check(ring[jj][m][0], i);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int row = (16 * jt + r) * nz;  // uniform
@@ -721,15 +736,12 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         // planes still in the ring that no chunk to the right shares
         for (int i = max(Lc, top - P); i <= top && (open || i < Lnext); ++i) flush(i);
 #pragma unroll
-        for (int m = 0; m < R; ++m)  // and those that it does: plane top - (top - m) mod R
-            mark(max(top - (top - m + R) % R, 0), ring[0][m][0]);
+        for (int m = 0; m < R; ++m)  // those still shared: slot m holds plane top - (top - m) mod R
+            check(ring[0][m][0], max(top - (top - m + R) % R, 0));
+        if (chk != chk) mark((~0ull >> (63 - top)) & (~0ull << Lc));
     }
     lds_barrier();  // left partial planes of every chunk in LDS
-    uint64_t bad = 0;
-#pragma unroll
-    for (int w = 0; w < kAM / 32; ++w)
-        bad |= (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)sm.bad[w]) << (32 * w);
-    bad &= (~0ull >> (64 - i1)) & (~0ull << i0);  // of this segment
+    const uint32_t bad_lo = sm.bad[0], bad_hi = sm.bad[1];
     if (open) {
         // every plane of the segment: the chunks that touch it, in order
         for (int e = tid; e < (i1 - i0) * plane; e += kAT) {
@@ -758,6 +770,10 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         for (int e = tid; e < (min(lo, i1) - i0) * plane; e += kAT) Gb[(int64_t)i0 * plane + e] = 0.0f;
         for (int e = tid; e < (i1 - hl) * plane; e += kAT) Gb[(int64_t)hl * plane + e] = 0.0f;
     }
+    const uint64_t bad =
+        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)bad_hi) << 32 |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)bad_lo)) &
+        (~0ull >> (64 - i1)) & (~0ull << i0);  // of this segment
     if (bad) {
         const int64_t vox = (int64_t)rx * ry * rz;
         adj_windows<P, DER>(ny, nz, ry, rz, mask, g + (int64_t)b * __builtin_popcount(mask) * vox,
