@@ -25,10 +25,10 @@
 // partial planes there in LDS, and the chunk to the left adds them to its
 // own after the workgroup's one barrier.  The z product's K steps cover the
 // 16-column groups of w inside the basis band of the wave's k tile; the y
-// product runs over all four row bands (its y basis operands are zero
-// outside each j tile's band).  The slice body is straight-line code, one
-// instance per (band width, one or two j tiles), so that the four z chains
-// (one per row band), the loads of the next slice and the y chains of a
+// product runs over all row bands of the slice, one, two or four by the
+// resolution (its y basis operands are zero outside each j tile's band).  The
+// slice body is straight-line code, one instance per (row bands, band width,
+// one or two j tiles), so that the z chains (one per row band), the loads of the next slice and the y chains of a
 // slice are scheduled together.  Fixed summation order, no floating-point
 // atomics: the result is deterministic.
 //
@@ -252,8 +252,9 @@ __device__ __forceinline__ void adj_windows(int ny, int nz, int ry, int rz, uint
 }
 
 // RAG: the rows of the cotangent are not whole 16-byte vectors (the values a
-// load takes from past its row's end are replaced by zeros)
-template <int P, bool DER, bool RAG>
+// load takes from past its row's end are replaced by zeros).  MB: the 16-row bands
+// of a slice, ry <= 16 MB
+template <int P, bool DER, bool RAG, int MB>
 __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots, int rx, int ry,
                                           int rz, uint32_t mask, const float *g, float *G, int b,
                                           int seg, int nseg, AmSmem<DER> &sm) {
@@ -512,8 +513,8 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         // values only: operands held for the whole block, the z basis at the
         // lane's w = 16 (q0 + q') + 4 gq + j for its k, the y basis at its 16
         // v positions for its j (zero outside each j tile's band, so the y
-        // product runs over all four row bands)
-        float bzs[4][4], by[4][4][kJT];
+        // product runs over all row bands)
+        float bzs[4][4], by[MB][4][kJT];
         if constexpr (!DER) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -521,7 +522,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                 for (int j = 0; j < 4; ++j)
                     bzs[q][j] = zval(16 * (q0 + q) + 4 * gq + j, k, sm.zN);
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
+            for (int mt = 0; mt < MB; ++mt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -541,12 +542,12 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         const int nch = __builtin_popcount(mask);
         const __amdgpu_buffer_rsrc_t rs = make_rsrc(g + (int64_t)b * nch * vox,
                                                     (uint32_t)(nch * vox * 4));
-        uint32_t roff[4], coff[4];
+        uint32_t roff[MB], coff[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            roff[t] = (uint32_t)(min(16 * t + l16, ry - 1) * rz * 4);
+        for (int t = 0; t < MB; ++t) roff[t] = (uint32_t)(min(16 * t + l16, ry - 1) * rz * 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
             coff[t] = (uint32_t)(min(16 * t + 4 * gq, (rz - 1) & ~3) * 4);
-        }
         const uint32_t sbytes = (uint32_t)(ry * rz * 4);
         // (the range check need not see the scalar offset: where a load may
         // leave the block, all of its offset is in the vector part)
@@ -561,9 +562,9 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         // the slice loop, straight-line code for each (nq, one or two j tiles)
         auto slices = [&](auto NQc, auto NJc) __attribute__((always_inline)) {
             constexpr int NQ = decltype(NQc)::value, NJ = decltype(NJc)::value;
-            auto loads = [&](uint32_t at, uint32_t dead, float4(&f)[4][NQ]) {
+            auto loads = [&](uint32_t at, uint32_t dead, float4(&f)[MB][NQ]) {
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt)
+                for (int mt = 0; mt < MB; ++mt)
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) f[mt][q] = load(at, dead, mt, min(q0 + q, 3));
             };
@@ -581,20 +582,20 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                 }
             };
           if constexpr (!DER) {
-            float4 ga[4][NQ];
+            float4 ga[MB][NQ];
             loads((uint32_t)ua * sbytes, 0u, ga);
             for (int u = ua; u <= ub; ++u) {
                 const int un = u < ub ? u + 1 : u;  // the next slice (the last one again at the end)
-                // z: four independent chains (one per 16-row band)
-                f32x4a Z[4];
+                // z: independent chains, one per 16-row band
+                f32x4a Z[MB];
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt) Z[mt] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int mt = 0; mt < MB; ++mt) Z[mt] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int q = 0; q < NQ; ++q)
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
 #pragma unroll
-                        for (int mt = 0; mt < 4; ++mt)
+                        for (int mt = 0; mt < MB; ++mt)
                             Z[mt] = mma4(val(ga[mt][q], q, j), bzs[q][j], Z[mt]);
                 // the next slice, in flight during the rest of this one
                 loads((uint32_t)un * sbytes, 0u, ga);
@@ -603,7 +604,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
 #pragma unroll
                 for (int jj = 0; jj < kJT; ++jj) Y[jj] = Yo[jj] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt)
+                for (int mt = 0; mt < MB; ++mt)
 #pragma unroll
                     for (int jj = 0; jj < NJ; ++jj) {
                         Y[jj] = mma4(by[mt][0][jj], Z[mt][0], Y[jj]);
@@ -632,24 +633,24 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
             // Z tile set is live at a time
             const uint32_t vb = (uint32_t)(vox * 4);
             // a channel that is not there reads zeros past the resource's end
-            auto fetch = [&](int u, int ch, float4(&f)[4][NQ]) __attribute__((always_inline)) {
+            auto fetch = [&](int u, int ch, float4(&f)[MB][NQ]) __attribute__((always_inline)) {
                 const bool has = mask & (1u << ch);
                 const uint32_t c = (uint32_t)__builtin_popcount(mask & ((1u << ch) - 1u));
                 loads(has ? c * vb + (uint32_t)u * sbytes : 0u, has ? 0u : 0x40000000u, f);
             };
-            float4 ga[4][NQ], gb[4][NQ];
+            float4 ga[MB][NQ], gb[MB][NQ];
             fetch(ua, 1, ga);
             fetch(ua, 0, gb);
             for (int u = ua; u <= ub; ++u) {
                 const int un = u < ub ? u + 1 : u;
                 int ln = lane;  // opaque: the operands stay in LDS
                 asm volatile("" : "+v"(ln));
-                f32x4a Z[4];
+                f32x4a Z[MB];
                 auto zero = [&](f32x4a *f, int n) __attribute__((always_inline)) {
 #pragma unroll
                     for (int m = 0; m < n; ++m) f[m] = f32x4a{0.0f, 0.0f, 0.0f, 0.0f};
                 };
-                auto zmul = [&](const float4(&f)[4][NQ], int d) __attribute__((always_inline)) {
+                auto zmul = [&](const float4(&f)[MB][NQ], int d) __attribute__((always_inline)) {
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
                         const float4 o = sm.op[0][d][nt][min(q0 + q, 3)][ln];
@@ -657,7 +658,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
 #pragma unroll
                         for (int j = 0; j < 4; ++j)
 #pragma unroll
-                            for (int mt = 0; mt < 4; ++mt)
+                            for (int mt = 0; mt < MB; ++mt)
                                 Z[mt] = mma4(val(f[mt][q], q, j), ov[j], Z[mt]);
                     }
                 };
@@ -665,7 +666,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                 f32x4a Yb[kJT], Yo[kJT], Yd[kJT];
                 auto ymul = [&](int d, f32x4a(&Y)[kJT]) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int mt = 0; mt < 4; ++mt)
+                    for (int mt = 0; mt < MB; ++mt)
 #pragma unroll
                         for (int jj = 0; jj < NJ; ++jj) {
                             const float4 o = sm.op[1][d][2 * jp + jj][mt][ln];
@@ -677,7 +678,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                 };
                 zero(Yd, kJT);
                 zero(Yo, kJT);
-                zero(Z, 4);
+                zero(Z, MB);
                 if (mask & 2u) zmul(ga, 0);
                 fetch(u, 3, ga);
                 if (mask & 2u) ymul(0, Yd);
@@ -685,13 +686,13 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
                 for (int jj = 0; jj < NJ; ++jj) Yd[jj] += Yo[jj];
                 zero(Yb, kJT);
                 zero(Yo, kJT);
-                zero(Z, 4);
+                zero(Z, MB);
                 if (mask & 1u) zmul(gb, 0);
                 fetch(u, 2, gb);
                 if (mask & 8u) zmul(ga, 1);
                 fetch(un, 1, ga);
                 if (mask & 9u) ymul(0, Yb);
-                zero(Z, 4);
+                zero(Z, MB);
                 if (mask & 4u) zmul(gb, 0);
                 fetch(un, 0, gb);
                 if (mask & 4u) ymul(1, Yb);
@@ -781,7 +782,7 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
     }
 }
 
-template <bool DER, bool RAG>
+template <bool DER, bool RAG, int MB>
 __global__ __launch_bounds__(kAT) void adjoint_kernel(const fa_block *blocks, int nseg,
                                                       const float *knots, int rx, int ry, int rz,
                                                       uint32_t mask, const float *g, float *G) {
@@ -791,17 +792,17 @@ __global__ __launch_bounds__(kAT) void adjoint_kernel(const fa_block *blocks, in
     const int b = blockIdx.x / nseg, seg = blockIdx.x - b * nseg;
     const fa_block &B = blocks[b];
     const int p = B.degree[0];
-    if (p == 3) adj_block<3, DER, RAG>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
-    else if (p == 2) adj_block<2, DER, RAG>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
-    else adj_block<1, DER, RAG>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
+    if (p == 3) adj_block<3, DER, RAG, MB>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
+    else if (p == 2) adj_block<2, DER, RAG, MB>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
+    else adj_block<1, DER, RAG, MB>(B, knots, rx, ry, rz, mask, g, G, b, seg, nseg, sm);
 }
 
-template <bool DER, bool RAG>
+template <bool DER, bool RAG, int MB>
 hipError_t launch(const fa_block *blocks, int nblocks, const float *knots, int rx, int ry, int rz,
                   uint32_t mask, const float *g, float *G, hipStream_t s) {
     // raise the dynamic LDS limit once per process (before any graph capture)
     static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&adjoint_kernel<DER, RAG>),
+        reinterpret_cast<const void *>(&adjoint_kernel<DER, RAG, MB>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(AmSmem<DER>));
     if (attr != hipSuccess) return attr;
     // one workgroup fits a CU: segments while a CU would be without one
@@ -809,13 +810,24 @@ hipError_t launch(const fa_block *blocks, int nblocks, const float *knots, int r
     const int64_t values = (int64_t)__builtin_popcount(mask) * rx * ry * rz;
     for (int b0 = 0; b0 < nblocks; b0 += kMostGroups) {
         const int n = std::min(nblocks - b0, kMostGroups);
-        hipLaunchKernelGGL((adjoint_kernel<DER, RAG>), dim3((unsigned)n * nseg), dim3(kAT),
+        hipLaunchKernelGGL((adjoint_kernel<DER, RAG, MB>), dim3((unsigned)n * nseg), dim3(kAT),
                            sizeof(AmSmem<DER>), s, blocks + b0, nseg, knots, rx, ry, rz, mask,
                            g + b0 * values, G);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+template <int MB>
+hipError_t launch_rows(const fa_block *blocks, int nblocks, const float *knots, int rx, int ry,
+                       int rz, uint32_t mask, const float *g, float *G, hipStream_t s) {
+    const bool rag = (rz & 3) != 0;
+    if (mask == 1u)
+        return rag ? launch<false, true, MB>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s)
+                   : launch<false, false, MB>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s);
+    return rag ? launch<true, true, MB>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s)
+               : launch<true, false, MB>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s);
 }
 
 }  // namespace
@@ -825,12 +837,13 @@ hipError_t launch_adjoint(const fa_block *blocks, int nblocks, const float *knot
     if (ry > kAM || rz > kAM) return hipErrorNotSupported;
     if (nblocks <= 0) return hipSuccess;
     mask &= 15u;
-    const bool rag = (rz & 3) != 0;
-    if (mask == 1u)
-        return rag ? launch<false, true>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s)
-                   : launch<false, false>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s);
-    return rag ? launch<true, true>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s)
-               : launch<true, false>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s);
+    // 16-row bands of the cotangent's slices that hold rows: products over the
+    // rows of no band are zeros.  Four at any resolution cost (20000 blocks of
+    // 16^3, mixed NCP and degree) values 1.41 ms, all channels 2.62; two 1.21 and
+    // 2.00; one 1.07 and 1.73.  4000 of 32^3: four 0.455 and 1.14, two 0.356, 0.746
+    return ry <= 16   ? launch_rows<1>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s)
+           : ry <= 32 ? launch_rows<2>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s)
+                      : launch_rows<4>(blocks, nblocks, knots, rx, ry, rz, mask, g, G, s);
 }
 
 }  // namespace fa
