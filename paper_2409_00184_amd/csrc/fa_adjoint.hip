@@ -37,6 +37,10 @@
 // 1 KB per channel and slice against 64 products), and two buffers hold the
 // channel in use and the one in flight.
 //
+// With two or more channels a segment whose lattice has few planes for its slices, or
+// more columns than two tiles hold, is summed along x first on the vector ALUs
+// (adj_planes): one set of y and z sums per plane instead of products per slice.
+//
 // A micro-model is split between `nseg` workgroups when there are fewer
 // micro-models than CUs: a segment owns the control planes [i0, i1), streams
 // the slices whose basis touches them (neighbours re-read an overlap of p
@@ -251,6 +255,172 @@ __device__ __forceinline__ void adj_windows(int ny, int nz, int ry, int rz, uint
     }
 }
 
+// Whether x first (adj_planes) is the faster form for a segment: `len` slices in X
+// chunks, `waves` = X * (k tiles) * (j tile pairs) in use, nq column groups and nj j
+// tiles per product, np planes of r - 1 = degree.  The sums estimate the two forms'
+// time in ns: a wave's products per slice at 22 ns, 40 where two waves share a SIMD;
+// rows and channels per slice, y and z sums per plane.  Coefficients by least squares
+// over 914 launches (NCP 4..48, cubic and not, degrees 1 to 3, 16^3 to 100 x 64 x 64,
+// one to four channels), which they meet to 16% and 13%.  A wrong choice costs more
+// than a missed one, so x first has to be estimated a fifth lower, with two channels
+// 30%, and one channel or more planes than slices stay with the products.  800 blocks
+// of 64^3, all channels, x first and matrix form: degree 1, NCP 40 1.33 and 2.69 ms,
+// NCP 20 0.80 and 1.13, NCP 16 0.72 and 0.68; degree 3 1.77 and 2.69, 0.98 and 1.13,
+// 0.92 and 0.75.
+template <int MB>
+__device__ __forceinline__ bool planes_first(int len, int X, int waves, int nq, int nj, int np,
+                                             int r, int ny, int ry, int rz, uint32_t mask) {
+    const int nch = __builtin_popcount(mask);
+    const int nyp = !!(mask & 2u) + !!(mask & 9u) + !!(mask & 4u);  // y products
+    const int products = 4 * MB * (nch * nq + nyp * nj);
+    const int m = 15000 + (len + X - 1) / X * (580 + products * (waves > kAW / 2 ? 40 : 22));
+    const int x = 7000 + len * (104 + MB * (42 * r + 61 * nch)) +
+                  np * (1043 + 13 * ry * r + ny * rz * r / 4);
+    return nch > 1 && np <= len && 10 * x < (nch > 2 ? 8 : 7) * m;
+}
+
+// The segment's planes with x first, on the vector ALUs: lane w, row wave + 8 m
+// of every slice; a thread keeps the p + 1 newest x sums of its columns,
+// and a plane whose last slice has passed goes to LDS, where y is summed
+// over each j's rows and z over each k's columns.  An infinite or NaN value meets
+// no weight outside its windows here.  Bound by the cotangent's reads where planes
+// are few (4.2 TB/s at 64^3, NCP 20, degree 1), else by the LDS reads of the y sums.
+// Two slices are in registers at four row bands and four below, where a slice is a
+// few KB (1000 blocks of 100 x 20 x 30, NCP 4 x 16 x 32, degree 1, in a kernel of this
+// form alone: 0.70 ms with two, 0.29 with four).
+template <int P, int MB>
+__device__ __forceinline__ void adj_planes(int ny, int nz, int ry, int rz, uint32_t mask,
+                                           const float *g, int64_t vox, float *Gb, int i0, int i1,
+                                           int slo, int shi, AmSmem<true> &sm) {
+    constexpr int R = P + 1, kRows = 2 * MB, kP = kAM * kWave;
+    constexpr int kDeep = MB == 4 ? 2 : 4;  // slices in registers
+    static_assert(3 * kP + 4 * kAM <= kLB, "x sums of a plane and supports");
+    static_assert(2 * kP * sizeof(float) <= sizeof(sm.op), "y sums of a plane");
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int plane = ny * nz;
+    float *H0 = sm.lb, *H2 = H0 + kP, *H3 = H2 + kP;
+    float *KB = reinterpret_cast<float *>(sm.op), *K3 = KB + kP;
+    // first and last position of each lattice index along y and z
+    int *lo = reinterpret_cast<int *>(H3 + kP), *hi = lo + 2 * kAM;
+    if (tid < 2 * kAM) {
+        lo[tid] = 0x7fffffff;
+        hi[tid] = -1;
+    }
+    lds_barrier();
+    for (int t = tid; t < ry + rz; t += kAT) {
+        const bool isy = t < ry;
+        const int pos = isy ? t : t - ry, s = (isy ? sm.ys : sm.zs)[pos];
+        for (int i = s - P; i <= s; ++i) {
+            atomicMin(&lo[(isy ? 0 : kAM) + i], pos);
+            atomicMax(&hi[(isy ? 0 : kAM) + i], pos);
+        }
+    }
+    const float *gw = g + min(lane, rz - 1);
+    const int64_t slice = (int64_t)ry * rz;
+    int row[kRows];
+#pragma unroll
+    for (int m = 0; m < kRows; ++m) row[m] = min(wave + kAW * m, ry - 1) * rz;
+    float hB[kRows][R], h2[kRows][R], h3[kRows][R];
+#pragma unroll
+    for (int m = 0; m < kRows; ++m)
+#pragma unroll
+        for (int r = 0; r < R; ++r) hB[m][r] = h2[m][r] = h3[m][r] = 0.0f;
+
+    auto emit = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 0; m < kRows; ++m) {
+            const int v = wave + kAW * m;
+            if (v < ry) {
+                H0[v * kWave + lane] = hB[m][0];
+                H2[v * kWave + lane] = h2[m][0];
+                H3[v * kWave + lane] = h3[m][0];
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                hB[m][r] = r < P ? hB[m][r + 1] : 0.0f;
+                h2[m][r] = r < P ? h2[m][r + 1] : 0.0f;
+                h3[m][r] = r < P ? h3[m][r + 1] : 0.0f;
+            }
+        }
+        if (i < i0) return;  // uniform: a neighbour's plane
+        lds_barrier();
+        for (int e = tid; e < ny * kWave; e += kAT) {
+            const int j = e >> 6, w = e & 63;
+            float kb = 0.0f, k3 = 0.0f;
+            for (int v = lo[j]; v <= hi[j]; ++v) {
+                const int r = j - (sm.ys[v] - P);
+                const float cb = entry(sm.yN, v, r);
+                kb = fmaf(cb, H0[v * kWave + w], kb);
+                kb = fmaf(entry(sm.yD, v, r), H2[v * kWave + w], kb);
+                k3 = fmaf(cb, H3[v * kWave + w], k3);
+            }
+            KB[e] = kb;
+            K3[e] = k3;
+        }
+        lds_barrier();
+        for (int e = tid; e < plane; e += kAT) {
+            const int j = e / nz, k = e - j * nz;
+            float acc = 0.0f;
+            for (int w = lo[kAM + k]; w <= hi[kAM + k]; ++w) {
+                const int r = k - (sm.zs[w] - P);
+                acc = fmaf(entry(sm.zN, w, r), KB[j * kWave + w], acc);
+                acc = fmaf(entry(sm.zD, w, r), K3[j * kWave + w], acc);
+            }
+            Gb[(int64_t)i * plane + e] = acc;
+        }
+        lds_barrier();
+    };
+
+    float f[kDeep][4][kRows];  // the slice in use and the next ones
+    auto fetch = [&](int u, float(&x)[4][kRows]) __attribute__((always_inline)) {
+        int c = 0;
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) {
+            if (mask >> ch & 1u) {
+                const float *gu = gw + (int64_t)c * vox + (int64_t)u * slice;
+#pragma unroll
+                for (int m = 0; m < kRows; ++m) x[ch][m] = gu[row[m]];
+                ++c;
+            } else {
+#pragma unroll
+                for (int m = 0; m < kRows; ++m) x[ch][m] = 0.0f;
+            }
+        }
+    };
+    int nxt = i0;  // the next plane to leave: window slot 0
+    auto use = [&](int u, const float(&x)[4][kRows]) __attribute__((always_inline)) {
+        const int s = __builtin_amdgcn_readfirstlane(sm.xS[u]);
+        for (; nxt < s - P; ++nxt) emit(nxt);
+        float cf[R], ef[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            cf[r] = entry(sm.xB, u, (s - P + r) % R);
+            ef[r] = entry(sm.xD, u, (s - P + r) % R);
+        }
+#pragma unroll
+        for (int m = 0; m < kRows; ++m)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                hB[m][r] = fmaf(cf[r], x[0][m], fmaf(ef[r], x[1][m], hB[m][r]));
+                h2[m][r] = fmaf(cf[r], x[2][m], h2[m][r]);
+                h3[m][r] = fmaf(cf[r], x[3][m], h3[m][r]);
+            }
+    };
+    if (slo < shi) {
+        nxt = min(nxt, __builtin_amdgcn_readfirstlane(sm.xS[slo]) - P);
+#pragma unroll
+        for (int d = 0; d < kDeep; ++d) fetch(min(slo + d, shi - 1), f[d]);
+        for (int u = slo; u < shi; u += kDeep)
+#pragma unroll
+            for (int d = 0; d < kDeep; ++d) {
+                if (u + d >= shi) break;  // uniform
+                use(u + d, f[d]);
+                fetch(min(u + d + kDeep, shi - 1), f[d]);
+            }
+    }
+    for (; nxt < i1; ++nxt) emit(nxt);
+}
+
 // RAG: the rows of the cotangent are not whole 16-byte vectors (the values a
 // load takes from past its row's end are replaced by zeros).  MB: the 16-row bands
 // of a slice, ry <= 16 MB
@@ -317,23 +487,6 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         const int d = j - (sm.ys[v] - P);
         return d >= 0 && d <= P ? pick4(tab[v], d) : 0.0f;
     };
-    if constexpr (DER) {
-        for (int e = tid; e < 4 * (kAM / 16) * 4 * kWave; e += kAT) {
-            const int l = e & (kWave - 1), q = (e >> 6) & 3, t = (e >> 8) & 3, d = (e >> 10) & 1;
-            const int p0 = 16 * q + 4 * (l >> 4), i = 16 * t + (l & 15);
-            float f[4];
-            if (e >> 11) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) f[r] = yval(p0 + r, i, d ? sm.yD : sm.yN);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) f[r] = zval(p0 + r, i, d ? sm.zD : sm.zN);
-            }
-            sm.op[e >> 11][d][t][q][l] = make_float4(f[0], f[1], f[2], f[3]);
-        }
-        lds_barrier();
-    }
-
     // waves: (chunk, j tile pair, k tile).  The segment's slices [slo, shi)
     // are split into X chunks of consecutive slices; each chunk after the
     // first starts at the first change of the span along x at or after slo +
@@ -419,6 +572,31 @@ __device__ __forceinline__ void adj_block(const fa_block &B, const float *knots,
         }
     }
     X = __builtin_amdgcn_readfirstlane(X);
+    if constexpr (DER) {
+        int nqm = 1;  // 16-column groups of the widest k tile's band
+        for (int t = 0; t < nkt; ++t) nqm = max(nqm, (sm.tw[1][t] >> 4) - (sm.tw[0][t] >> 4) + 1);
+        if (__builtin_amdgcn_readfirstlane(planes_first<MB>(
+                len, X, X * W1, nqm, min(2, njt), i1 - i0, P + 1, ny, ry, rz, mask))) {
+            const int64_t vox = (int64_t)rx * ry * rz;
+            adj_planes<P, MB>(ny, nz, ry, rz, mask, g + (int64_t)b * __builtin_popcount(mask) * vox,
+                              vox, G + B.ctrl_off, i0, i1, slo, shi, sm);
+            return;
+        }
+        for (int e = tid; e < 4 * (kAM / 16) * 4 * kWave; e += kAT) {
+            const int l = e & (kWave - 1), q = (e >> 6) & 3, t = (e >> 8) & 3, d = (e >> 10) & 1;
+            const int p0 = 16 * q + 4 * (l >> 4), i = 16 * t + (l & 15);
+            float f[4];
+            if (e >> 11) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) f[r] = yval(p0 + r, i, d ? sm.yD : sm.yN);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) f[r] = zval(p0 + r, i, d ? sm.zD : sm.zN);
+            }
+            sm.op[e >> 11][d][t][q][l] = make_float4(f[0], f[1], f[2], f[3]);
+        }
+        lds_barrier();
+    }
     ua = __builtin_amdgcn_readfirstlane(ua);
     ue = __builtin_amdgcn_readfirstlane(ue);
     const int c = cw;
