@@ -48,8 +48,8 @@
 //
 // Bound by the matrix cores of the busiest SIMD and the cotangent's reads:
 // values of 256 blocks of 64^3, NCP 16..32, 84 us (3.2 TB/s); all channels of
-// 128 blocks, NCP 8..32, 195 us (2.8 TB/s), where a form on the vector ALUs,
-// one workgroup per block with three barriers per control plane, took 914.
+// 128 blocks, NCP 8..32, 167 us (3.2 TB/s), 195 with every block on the matrix
+// cores, 914 with every block on the vector ALUs and one workgroup of 16 waves each.
 //
 // Operand layout of v_mfma_f32_16x16x4f32 (checked on the device): lane l
 // holds A[l%16][l/16] and B[l/16][l%16] and receives D[4(l/16)+r][l%16].
@@ -166,7 +166,7 @@ __device__ __forceinline__ float entry(const float4 *tab, int i, int d) {
 // window on each axis and no others.  Only workgroups that found such a value
 // come here, for the marked planes.  Bound by the latency of its sums' LDS reads:
 // 128 blocks of 64^3, all channels, one NaN in each, 0.55 ms at NCP 32, 1.4 at
-// 8..32, 1.9 at 4 (finite 0.15, 0.20, 0.18).
+// 8..32, 1.9 at 4 (finite 0.15, 0.17, 0.18).
 template <int P, bool DER>
 __device__ __forceinline__ void adj_windows(int ny, int nz, int ry, int rz, uint32_t mask,
                                             const float *g, int64_t vox, float *Gb, uint64_t bad,
