@@ -296,15 +296,16 @@ fa_status fa_render_rays(const fa_block *blocks, int32_t nblocks, const int32_t 
  * fit of the lattice to samples y on the block's grid, this is the fit's
  * gradient: the step model(NCP, degree) of Alg. 1 (Sec. 4.2.1) solves that
  * fit for every candidate NCP.  Deterministic (fixed summation order, no
- * floating-point atomics; the order depends on res, mask and nblocks).  An
- * infinite or NaN cotangent value reaches the lattice values whose basis
- * window holds its grid position, and no others.
+ * floating-point atomics; the order depends on res, mask, nblocks and the
+ * block's own NCP, degree and knots).  An infinite or NaN cotangent value
+ * reaches the lattice values whose basis window holds its grid position, and
+ * no others.
  *   grad_out   device FP32 [nblocks][popcount(mask)][res0][res1][res2]
  *   grad_ctrl  device FP32 lattice layout (same offsets as ctrl); the
  *              lattices of the blocks are overwritten, other elements are
  *              left untouched
  * res[1] and res[2] (the y and z resolutions) must be at most 64: a wave
- * holds an x slice's y and z extent as four 16-row bands of four 16-column
+ * holds an x slice's y and z extent as up to four 16-row bands of four 16-column
  * groups in registers (FA_ERR_UNSUPPORTED above 64; res[0] takes up to
  * FA_MAX_RES).
  */
